@@ -117,8 +117,9 @@ int dirac_apply_ex(qcd_field f, const void *in, void *out, int nrhs, qcd_prec io
 
 /* dirac_apply for callers that cannot allocate device memory (code under
  * HIP graph capture, serving loops, harnesses that forbid allocation): the
- * same operator and arguments, with the input and output staged in the
- * library's internal layout in a static device array of 64 MiB per GPU
+ * same operator and arguments; what has to be staged in the library's internal
+ * layout (io and vector precision differ, unaligned or overlapping vectors,
+ * launch choices set) is staged in a static device array of 64 MiB per GPU
  * (held from the library's first use of that GPU until the process ends)
  * instead of workspace that grows on demand; no device memory is allocated
  * and no profiling events are created.  Staging needs 2 x nrhs x V x 96
@@ -423,7 +424,10 @@ int gauss_smear(qcd_field f, const void *in, void *out, int nrhs, qcd_prec io, d
 
 /* Launch choices of a handle's Dirac stencil and Schwarz sweeps, for the
  * autotuner (defaults: block-staged, automatic, lexicographic, automatic,
- * 1, 1):
+ * 1, 1).  The stencil choices speak of the kernels on the internal layout,
+ * which the solvers use; with all of them at their defaults, dirac_apply on
+ * 16-byte aligned vectors of the operator's own vector type runs on the
+ * canonical vectors directly:
  * QCD_TUNE_STENCIL_BLOCK  1 = one workgroup per Schwarz block with the
  *                         block's spinors staged in LDS (when it fits),
  *                         0 = site tiles;

@@ -133,4 +133,19 @@ inline void build_block_tables(const int b[4], const int nb[4], int bc_t, BlockT
     }
 }
 
+// Tiles of the canonical-vector stencil: consecutive positions (a position is a
+// site of each parity), the largest divisor of a block's Vbh positions that is
+// at most `most`, or several whole blocks where a block is smaller (a number of
+// them that divides Nb).
+inline int tile_positions(int Vbh, int Nb, int most) {
+    if (Vbh > most) {
+        int P = most;
+        while (Vbh % P) --P;
+        return P;
+    }
+    int m = most / Vbh;
+    while (Nb % m) --m;
+    return m * Vbh;
+}
+
 }  // namespace dfl

@@ -725,6 +725,7 @@ static int field_create_common(const qcd_lattice *lat, const double2 *canon, hip
     f->face_cap = bt.face_cap;
     for (int mu = 0; mu < 4; ++mu) f->nface[mu] = bt.nface[mu];
     f->nface_tot = bt.nface_tot;
+    f->tile_pos = tile_positions(g.Vbh, g.Nb, CANON_TILE);
     if (!dev_alloc(f->device, (void **)&f->bface, sizeof(int) * bt.fl.size()) ||
         !dev_alloc(f->device, (void **)&f->bfsrc, sizeof(int) * bt.fsrc.size()) ||
         !dev_alloc(f->device, (void **)&f->bfnb, sizeof(int) * bt.fnb.size()))

@@ -604,6 +604,9 @@ __device__ inline R nb_sign(int e) { return e < 0 ? R(-1) : R(1); }
 // for which it reaches 2^32.
 constexpr unsigned long long MAX_OFFSET_BYTES_PER_SITE = 384;
 
+// positions per tile of the canonical-vector kernels, at most
+constexpr int CANON_TILE = 128;
+
 struct Geom {
     int L[4], b[4], nb[4];
     long V, Vh;
@@ -632,6 +635,7 @@ struct qcd_field_s {
     // antiperiodic time boundary
     int *bfnb = nullptr;
     int nface_tot = 0;       // sum of nface: face entries per block
+    int tile_pos = 0;        // positions per tile of the canonical-vector stencil
     int *int_of = nullptr;   // [V] lexicographic -> internal
     int *lex_of = nullptr;   // [V] internal -> lexicographic
     int *border = nullptr;   // [Nb] lexicographic block -> block index in memory (colour-major)
@@ -735,6 +739,15 @@ int pack_spinor(qcd_field f, const void *canon, qcd_prec io, void *internal, qcd
                 hipStream_t s);
 int unpack_spinor(qcd_field f, const void *internal, qcd_prec vec, void *canon, qcd_prec io, int nrhs,
                   hipStream_t s);
+
+// the same through LDS tiles, and the operator on canonical vectors (canon.hip);
+// canonical pointers must be 16-byte aligned (canon_aligned)
+bool canon_aligned(const void *p);
+bool canon_route(qcd_field f, const void *in, const void *out, int nrhs, qcd_prec io, qcd_prec storage, qcd_prec vin,
+                 qcd_prec vout);
+int pack_tiles(qcd_field f, const void *canon, qcd_prec io, void *internal, qcd_prec vec, int nrhs, hipStream_t s);
+int unpack_tiles(qcd_field f, const void *internal, qcd_prec vec, void *canon, qcd_prec io, int nrhs, hipStream_t s);
+int dirac_canon(qcd_field f, const void *in, void *out, int nrhs, qcd_prec storage, hipStream_t s);
 
 // one source vector built in the internal FP64 layout: Z2 noise vector
 // `index` of the stream `seed`; the sequential source of one canonical

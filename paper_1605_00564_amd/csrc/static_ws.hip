@@ -1,9 +1,9 @@
 // The Dirac operator for callers that cannot allocate device memory (code
 // under HIP graph capture, serving loops, harnesses that forbid it).
 //
-// dirac_apply stages its input and output in the library's internal layout
-// in workspace buffers that grow on demand.  This variant stages them in a
-// fixed device array instead: `scratch`, of SCRATCH_BYTES, one copy per GPU,
+// Where dirac_apply stages its input and output in the library's internal
+// layout, it does so in workspace buffers that grow on demand.  This variant
+// stages them in a fixed device array instead: `scratch`, of SCRATCH_BYTES, one copy per GPU,
 // held from the first time the library runs on that GPU until the process
 // ends.  The array's name is a host-side stand-in in host code; its device
 // address is looked up once per device (hipGetSymbolAddress, with that
@@ -79,9 +79,15 @@ extern "C" int dirac_apply_noalloc(qcd_field f, const void *in, void *out, int n
     // no profiling events either (their creation may allocate)
     const bool was = nosync();
     set_nosync(true);
-    int rc = pack_spinor(f, in, io, a, vec, nrhs, s);
-    if (rc == 0) rc = dirac_internal2(f, a, vec, b, vec, nrhs, storage, s);
-    if (rc == 0) rc = unpack_spinor(f, b, vec, out, io, nrhs, s);
+    int rc;
+    if (canon_route(f, in, out, nrhs, io, storage, vec, vec)) {
+        // the operator on the canonical vectors themselves: nothing to stage
+        rc = dirac_canon(f, in, out, nrhs, storage, s);
+    } else {
+        rc = pack_spinor(f, in, io, a, vec, nrhs, s);
+        if (rc == 0) rc = dirac_internal2(f, a, vec, b, vec, nrhs, storage, s);
+        if (rc == 0) rc = unpack_spinor(f, b, vec, out, io, nrhs, s);
+    }
     set_nosync(was);
     return rc;
 }
