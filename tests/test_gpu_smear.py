@@ -87,3 +87,24 @@ def test_smearing_degenerate_parameters():
         assert torch.equal(dfl.gauss_smear(s["fld"], x, kappa, n), x), (kappa, n)
     # back to the parameters the other tests use
     s["fld"].ape_smear(ALPHA, NAPE)
+
+
+@pytest.mark.parametrize("dims,block", [((4, 8, 12, 4), (2, 4, 2, 2)), ((8, 4, 8, 20), (4, 2, 4, 2))])
+@pytest.mark.parametrize("n", [1, 3, 4, 6])
+def test_smearing_on_uneven_lattices(dims, block, n):
+    """Extents that all differ (every neighbour stride its own) and counts of
+    vectors on both sides of the groups of four; the output may be the input."""
+    torch, dfl = _gpu()
+    U = synth.gauge_field(dims, 0.4, 3)
+    fld = dfl.Field(dims, block, 0.124, 1.5, U)
+    fld.ape_smear(ALPHA, 3)
+    Us = smear.ape_smear(dims, U, ALPHA, 3)
+    assert np.abs(fld.ape_links().cpu().numpy() - Us[:, 1:]).max() <= 1e-13
+    x = synth.gaussian_spinor(dims, n, 6003)
+    for steps in (1, 4):
+        ref = smear.gauss_smear(dims, Us, x, 0.7, steps)
+        xt = torch.from_numpy(x).cuda()
+        got = dfl.gauss_smear(fld, xt, 0.7, steps).cpu().numpy()
+        assert np.linalg.norm(got - ref) / np.linalg.norm(ref) <= 1e-12
+        dfl.gauss_smear(fld, xt, 0.7, steps, out=xt)
+        assert np.array_equal(xt.cpu().numpy(), got)
