@@ -63,6 +63,19 @@ def test_two_point_contraction_matches_oracle(dtype):
         assert err <= 1e-12
 
 
+@pytest.mark.parametrize("dims,block", [((4, 4, 4, 4), (2, 2, 2, 2)), ((4, 12, 8, 20), (2, 2, 4, 2)),
+                                        ((64, 4, 20, 20), (4, 2, 2, 2))])
+def test_two_point_contraction_site_groups(dims, block):
+    """One, one and several groups of 16 sites per workgroup, the last
+    workgroup of a timeslice not full."""
+    torch, dfl = _gpu()
+    U, fld = field(dims, block)
+    prop = random_prop(dims, 5003)
+    got = dfl.nucleon_2pt(fld, torch.from_numpy(prop).cuda(), 1).cpu().numpy()
+    ref = nuc.nucleon_2pt(prop, dims, 1)
+    assert relmax(got, ref) <= 1e-12
+
+
 @pytest.mark.parametrize("flavour", ["u", "d"])
 @pytest.mark.parametrize("direction,t_s", [("forward", 6), ("backward", 2), ("forward", DIMS[0] - 1),
                                            ("backward", 0)])
