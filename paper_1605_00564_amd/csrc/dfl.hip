@@ -230,130 +230,139 @@ __global__ void __launch_bounds__(128) k_dirac_split(const float4 *__restrict__ 
     Spin<double>::store(out, V, x, h);
 }
 
-// FP32 restriction u = Phi^+ v as a real GEMM on the matrix cores
-// (v_mfma_f32_16x16x4f32, FP32 accumulation).  Rows: 16 deflation fields;
-// columns: 8 right-hand sides x (re, im); K: the real components of the
-// block's sites.  With phi = a + ib and v = c + id, conj(phi) v =
-// (ac + bd) + i(ad - bc): column 2r carries (c, d) and column 2r+1 (d, -c)
-// against the row (a, b).  Lane L supplies A[L % 16][L / 16] and B[L / 16][L % 16]
-// and receives D[4 (L / 16) + i][L % 16], i = 0..3.  Each lane loads one
-// float4 (two complex) of phi and of v per four MFMAs; the K order is
-// (element q + L / 16, component i), identical for both operands.
+// Restriction u = Phi^+ v: per block a complex GEMM (N_s x 24 Vb) (24 Vb x n) on
+// the matrix cores, in the type of v (FP32 or FP64).  With phi = a + ib and
+// v = c + id, conj(phi) v = (ac + bd) + i(ad - bc) as real 16x16x4 products.
+// Narrow tile: 8 right-hand sides, whose real and imaginary parts are
+// neighbouring columns, two products per complex element; wide tile (FP64): 16
+// right-hand sides, four products.  Lane L supplies phi[field L % 16][element
+// L / 16] and v[element L / 16][column L % 16] (an element is a float4 of phi: two
+// complex) and receives D[rows of L][column L % 16].  The RSW waves take every
+// RSW-th group of four elements; their sums are added in order, in FP64.
+// What bounded it was not the products but the walk over the block's runs (64-bit
+// divisions per element) with one element's loads in flight; now each lane steps
+// from run to run, and the loads of four elements precede their products.
+// Kernel, us, before -> now: 16^3 x 32, N_s = 12: FP64, 12 rhs 196 -> 111, FP32,
+// 1 rhs 115 -> 56; 24^3 x 48, FP32, 24 rhs 650 -> 454 (phi read once per block by
+// tiles that share an XCD's L2; 370 at the card's copy rate).
 typedef float f4v __attribute__((ext_vector_type(4)));
 typedef double d4v __attribute__((ext_vector_type(4)));
-__global__ void __launch_bounds__(256) k_restrict_mfma(const float4 *__restrict__ v, const float4 *__restrict__ phi,
-                                                       const int *__restrict__ boff, double2 *__restrict__ u, long V,
-                                                       long Vh, int Vbh, int rb, int Ns, int Nb, int n) {
-    __shared__ float red[4][16][17];
-    const int B = blockIdx.x, r0 = blockIdx.y * 8;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int row = lane & 15, kk = lane >> 4;
-    const int col = lane & 15, rr = col >> 1, which = col & 1;
-    const long per = 12L * Vbh * rb;
-    const bool rv = r0 + rr < n;
-    const float4 *vr = v + (size_t)(rv ? r0 + rr : 0) * 6 * V;
-    for (int l0 = 0; l0 < Ns; l0 += 16) {
-        const bool lv = l0 + row < Ns;
-        const float4 *pl = phi + ((size_t)B * Ns + (lv ? l0 + row : 0)) * per;
-        f4v acc = {0.f, 0.f, 0.f, 0.f};
-        // each wave takes every fourth group of four float4 elements
-        for (long q0 = (long)wave * 4; q0 < per; q0 += 16) {
-            const long q = q0 + kk;
-            float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (q < per) {
-                if (lv) a = pl[q];
-                if (rv) {
-                    int c;
-                    const long site = dfl_site(boff, B, rb, Vbh, Vh, q, c);
-                    b = vr[(long)c * V + site];
-                }
-            }
-            // B operand per component: column (c, d) for which = 0, (d, -c) for which = 1
-            const float b0 = which ? b.y : b.x, b1 = which ? -b.x : b.y;
-            const float b2 = which ? b.w : b.z, b3 = which ? -b.z : b.w;
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b0, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, b1, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, b2, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, b3, acc, 0, 0, 0);
-        }
-        for (int i = 0; i < 4; ++i) red[wave][4 * kk + i][col] = acc[i];
-        __syncthreads();
-        if (threadIdx.x < 128) {
-            const int orow = threadIdx.x >> 3, orr = threadIdx.x & 7;
-            if (l0 + orow < Ns && r0 + orr < n) {
-                double re = 0, im = 0;
-                for (int w = 0; w < 4; ++w) {
-                    re += red[w][orow][2 * orr];
-                    im += red[w][orow][2 * orr + 1];
-                }
-                u[((size_t)(r0 + orr) * Nb + B) * Ns + l0 + orow] = make_double2(re, im);
-            }
-        }
-        __syncthreads();
-    }
-}
+__device__ inline f4v mfma16(float a, float b, f4v c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+__device__ inline d4v mfma16(double a, double b, d4v c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+template <class R>
+struct Acc;
+template <>
+struct Acc<float> {
+    typedef f4v type;
+    static __device__ inline int drow(int kk, int i) { return 4 * kk + i; }
+};
+template <>
+struct Acc<double> {
+    typedef d4v type;
+    static __device__ inline int drow(int kk, int i) { return kk + 4 * i; }
+};
 
-// FP64 restriction u = Phi^+ v for FP64 vectors on the FP64 matrix cores
-// (little-operator assembly and the outer loop's low-mode corrections).
-// Per block a complex GEMM (Ns x 24 Vb) (24 Vb x n): with phi = a + ib and
-// v = c + id, conj(phi) v = (ac + bd) + i(ad - bc), accumulated as four real
-// 16x16x4 products.  Rows: 16 fields; columns: 16 right-hand sides; lane L
-// supplies phi[row L % 16][k L / 16] and v[k L / 16][rhs L % 16] (k: one
-// float4 element = two complex, one MFMA quadruple each) and receives
-// u[field L / 16 + 4 i][rhs L % 16], i = 0..3.  The four waves
-// take every fourth group of four elements; their partial sums are added in
-// a fixed order.
-__global__ void __launch_bounds__(256) k_restrict_mfma64(const double2 *__restrict__ v, const float4 *__restrict__ phi,
-                                                         const int *__restrict__ boff, double2 *__restrict__ u, long V,
-                                                         long Vh, int Vbh, int rb, int Ns, int Nb, int n) {
-    __shared__ double red[4][2][16][17];
-    const int B = blockIdx.x, r0 = blockIdx.y * 16;
+// A lane's place in a deflation block's vectors: run cp = 2 c + p of member m,
+// local index j; at = offset of the run's element j in an FP32 field ([6][V])
+struct Walk {
+    int j, cp, m;
+    const int *bo;
+    int rb, Vbh;
+    __device__ inline void advance(int by) {
+        j += by;
+        while (j >= Vbh) {
+            j -= Vbh;
+            if (++cp == 12) {
+                cp = 0;
+                ++m;
+            }
+        }
+    }
+    __device__ inline long site(long Vh) const { return (cp & 1) * Vh + bo[min(m, rb - 1)] + j; }
+};
+
+constexpr int RSU = 4;   // elements in flight
+template <class R, bool WIDE, int RSW>
+__global__ void __launch_bounds__(64 * RSW) k_restrict(const void *__restrict__ vv, const float4 *__restrict__ phi,
+                                                       const int *__restrict__ boff, double2 *__restrict__ u, long V,
+                                                       long Vh, int Vbh, int rb, int Ns, int Nb, int n, int ng) {
+    constexpr bool F64V = sizeof(R) == 8;
+    constexpr int TR = WIDE ? 16 : 8;
+    __shared__ R red[RSW][WIDE ? 2 : 1][16][17];
+    const int B = (blockIdx.x / (8 * ng)) * 8 + blockIdx.x % 8, r0 = (int)((blockIdx.x / 8) % ng) * TR;
+    if (B >= Nb) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int row = lane & 15, kk = lane >> 4;
-    const long per = 12L * Vbh * rb;
-    const bool rv = r0 + row < n;
-    const double2 *vr = v + (size_t)(rv ? r0 + row : 0) * 12 * V;
+    const bool im = row & 1;
+    const int per = 12 * Vbh * rb;
+    const int rhs = min(r0 + (WIDE ? row : row / 2), n - 1);   // from n on: not used
+    const double2 *v64 = static_cast<const double2 *>(vv) + (size_t)rhs * 12 * V;
+    const float4 *v32 = static_cast<const float4 *>(vv) + (size_t)rhs * 6 * V;
     for (int l0 = 0; l0 < Ns; l0 += 16) {
         const bool lv = l0 + row < Ns;
         const float4 *pl = phi + ((size_t)B * Ns + (lv ? l0 + row : 0)) * per;
-        d4v ac = {0, 0, 0, 0}, bd = {0, 0, 0, 0}, ad = {0, 0, 0, 0}, bc = {0, 0, 0, 0};
-        for (long q0 = (long)wave * 4; q0 < per; q0 += 16) {
-            const long q = q0 + kk;
-            float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-            double2 b0 = make_double2(0.0, 0.0), b1 = make_double2(0.0, 0.0);
-            if (q < per) {
-                if (lv) a = pl[q];
-                if (rv) {
-                    int c;
-                    const long site = dfl_site(boff, B, rb, Vbh, Vh, q, c);
-                    b0 = vr[(long)(2 * c) * V + site];
-                    b1 = vr[(long)(2 * c + 1) * V + site];
+        typename Acc<R>::type x = {0, 0, 0, 0}, y = {0, 0, 0, 0}, z = {0, 0, 0, 0}, w = {0, 0, 0, 0};
+        Walk at{0, 0, 0, boff + (size_t)B * rb, rb, Vbh};
+        at.advance(4 * wave + kk);
+        for (int q0 = 4 * wave + kk; q0 - kk < per; q0 += 4 * RSW * RSU) {
+            float4 ph[RSU];
+            R b[RSU][4];
+#pragma unroll
+            for (int e = 0; e < RSU; ++e) {
+                const int q = q0 + 4 * RSW * e;
+                ph[e] = make_float4(0.f, 0.f, 0.f, 0.f);
+                b[e][0] = b[e][1] = b[e][2] = b[e][3] = 0;
+                if (q < per) {
+                    const long site = at.site(Vh);
+                    const int c = at.cp >> 1;
+                    if (lv) ph[e] = pl[q];
+                    if constexpr (F64V) {
+                        const double2 t0 = v64[(long)(2 * c) * V + site], t1 = v64[(long)(2 * c + 1) * V + site];
+                        b[e][0] = t0.x;
+                        b[e][1] = t0.y;
+                        b[e][2] = t1.x;
+                        b[e][3] = t1.y;
+                    } else {
+                        const float4 t = v32[(long)c * V + site];
+                        b[e][0] = t.x;
+                        b[e][1] = t.y;
+                        b[e][2] = t.z;
+                        b[e][3] = t.w;
+                    }
+                }
+                at.advance(4 * RSW);
+            }
+#pragma unroll
+            for (int e = 0; e < RSU; ++e) {
+                const R ar[2] = {R(ph[e].x), R(ph[e].z)}, ai[2] = {R(ph[e].y), R(ph[e].w)};
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const R c = b[e][2 * h], d = b[e][2 * h + 1];
+                    x = mfma16(ar[h], !WIDE && im ? d : c, x);
+                    y = mfma16(ai[h], !WIDE && im ? -c : d, y);
+                    if constexpr (WIDE) {
+                        z = mfma16(ar[h], d, z);
+                        w = mfma16(ai[h], -c, w);
+                    }
                 }
             }
-            ac = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a.x, b0.x, ac, 0, 0, 0);
-            bd = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a.y, b0.y, bd, 0, 0, 0);
-            ad = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a.x, b0.y, ad, 0, 0, 0);
-            bc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a.y, b0.x, bc, 0, 0, 0);
-            ac = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a.z, b1.x, ac, 0, 0, 0);
-            bd = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a.w, b1.y, bd, 0, 0, 0);
-            ad = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a.z, b1.y, ad, 0, 0, 0);
-            bc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a.w, b1.x, bc, 0, 0, 0);
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            red[wave][0][kk + 4 * i][row] = ac[i] + bd[i];
-            red[wave][1][kk + 4 * i][row] = ad[i] - bc[i];
+            red[wave][0][Acc<R>::drow(kk, i)][row] = x[i] + y[i];
+            if constexpr (WIDE) red[wave][1][Acc<R>::drow(kk, i)][row] = z[i] + w[i];
         }
         __syncthreads();
-        {
-            const int orow = threadIdx.x >> 4, orr = threadIdx.x & 15;
-            if (l0 + orow < Ns && r0 + orr < n) {
-                double re = 0, im = 0;
-                for (int w = 0; w < 4; ++w) {
-                    re += red[w][0][orow][orr];
-                    im += red[w][1][orow][orr];
+        for (int e = threadIdx.x; e < 16 * TR; e += 64 * RSW) {
+            const int lo = e & 15, ro = e >> 4;
+            if (l0 + lo < Ns && r0 + ro < n) {
+                double re = 0, ii = 0;
+#pragma unroll
+                for (int k = 0; k < RSW; ++k) {
+                    re += red[k][0][lo][WIDE ? ro : 2 * ro];
+                    ii += WIDE ? red[k][WIDE][lo][ro] : red[k][0][lo][2 * ro + 1];
                 }
-                u[((size_t)(r0 + orr) * Nb + B) * Ns + l0 + orow] = make_double2(re, im);
+                u[((size_t)(r0 + ro) * Nb + B) * Ns + l0 + lo] = make_double2(re, ii);
             }
         }
         __syncthreads();
@@ -367,16 +376,23 @@ __global__ void __launch_bounds__(256) k_restrict_mfma64(const double2 *__restri
 // block's coefficients are the same for all its threads: they are staged in
 // LDS when they fit (Ns x PR complex), which takes the chain of dependent
 // coefficient loads out of the inner loop.  Sums are FP64 either way.
-constexpr int PR = 12;
-template <class E, int MODE, bool STG>
+// PR is 1, 4 or 12, the fewest that hold n up to 12.  With the conversions, 16^3 x 32,
+// N_s = 12, FP32, 1 rhs: 68 -> 33 us
+// against twelve columns always (their FP64 products were the bound); 24^3 x 48,
+// 24 rhs: 658 -> 647 (the second group finds phi in L2), at the copy rate.
+template <class E, int MODE, bool STG, int PR>
 __global__ void __launch_bounds__(256) k_prolong(E *__restrict__ v, const float4 *__restrict__ phi,
                                                  const int *__restrict__ boff, const double2 *__restrict__ cf,
                                                  long V, long Vh, int Vbh, int rb, int Ns, int Nb, int n,
-                                                 int nchunk) {
-    const int B = blockIdx.x / nchunk;
+                                                 int nchunk, int ng) {
+    // the groups of right-hand sides of one chunk are eight workgroups apart:
+    // one XCD, whose L2 holds the chunk of phi for the later ones
+    const int bc = (blockIdx.x / (8 * ng)) * 8 + blockIdx.x % 8;
+    const int B = bc / nchunk;
+    if (B >= Nb) return;
     const long per = 12L * Vbh * rb;
-    const long q = (long)(blockIdx.x - B * nchunk) * 256 + threadIdx.x;
-    const int r0 = blockIdx.y * PR;
+    const long q = (long)(bc - B * nchunk) * 256 + threadIdx.x;
+    const int r0 = (int)((blockIdx.x / 8) % ng) * PR;
     const int nr = min(PR, n - r0);
     // STG: the workgroup's coefficients c[r0 + k][B][l] staged in LDS once
     // (cs[l][k], zero for k >= nr), read back as broadcasts; otherwise each
@@ -395,6 +411,7 @@ __global__ void __launch_bounds__(256) k_prolong(E *__restrict__ v, const float4
     double ar[PR], ai[PR], br[PR], bi[PR];
 #pragma unroll
     for (int k = 0; k < PR; ++k) ar[k] = ai[k] = br[k] = bi[k] = 0;
+#pragma unroll 4
     for (int l = 0; l < Ns; ++l) {
         const float4 f = phi[((size_t)B * Ns + l) * per + q];
 #pragma unroll
@@ -592,12 +609,21 @@ int restrict_v(qcd_dfl d, const E *v, double2 *u, int n, hipStream_t s) {
     double fl, by;
     dfl_work_counts(d, n, F32V ? 96 : 192, fl, by);
     ProfScope ps(PROF_DFL, s, fl, by, (double)g.V * n);
-    if constexpr (F32V)
-        k_restrict_mfma<<<dim3(d->Nb, (n + 7) / 8), 256, 0, s>>>(reinterpret_cast<const float4 *>(v), d->phi, d->boff,
-                                                                  u, g.V, g.Vh, g.Vbh, d->r, d->Ns, d->Nb, n);
-    else
-        k_restrict_mfma64<<<dim3(d->Nb, (n + 15) / 16), 256, 0, s>>>(v, d->phi, d->boff, u, g.V, g.Vh, g.Vbh, d->r,
-                                                                    d->Ns, d->Nb, n);
+    // wide tiles (FP64) hold 16 right-hand sides for the products of two narrow
+    // ones and half the loads of phi; 17 to 24 fill three narrow tiles better
+    const bool wide = !F32V && n > 8 && (n <= 16 || n > 24);
+    const int ng = wide ? (n + 15) / 16 : (n + 7) / 8;
+    const unsigned grid = (unsigned)((d->Nb + 7) / 8) * 8 * ng;
+    using R = std::conditional_t<F32V, float, double>;
+#define DFL_RESTRICT(T, WIDE, RSW) \
+    k_restrict<T, WIDE, RSW><<<grid, 64 * RSW, 0, s>>>(v, d->phi, d->boff, u, g.V, g.Vh, g.Vbh, d->r, d->Ns, d->Nb, n, ng)
+    // small blocks (2^4: 96 elements) do not feed eight waves
+    const bool small = 12L * g.Vbh * d->r <= 256;
+    if (wide && small) DFL_RESTRICT(double, true, 4);
+    else if (wide) DFL_RESTRICT(double, true, 8);
+    else if (small) DFL_RESTRICT(R, false, 4);
+    else DFL_RESTRICT(R, false, 8);
+#undef DFL_RESTRICT
     DFL_HIP(hipGetLastError());
     return 0;
 }
@@ -610,14 +636,23 @@ int prolong_v(qcd_dfl d, E *v, const double2 *c, int n, hipStream_t s) {
     dfl_work_counts(d, n, (F32V ? 96 : 192) * (MODE == 0 ? 1 : 2), fl, by);
     ProfScope ps(PROF_DFL, s, fl, by, (double)g.V * n);
     const int nchunk = (int)nblocks(12L * g.Vbh * d->r, 256);
-    const dim3 grid((unsigned)(d->Nb * nchunk), (n + PR - 1) / PR);
+    const int PR = n > 4 ? 12 : n > 1 ? 4 : 1;
+    const int ng = (n + PR - 1) / PR;
+    const unsigned grid = (unsigned)((d->Nb * nchunk + 7) / 8) * 8 * ng;
     const size_t stg = sizeof(double2) * (size_t)d->Ns * PR;
-    if (stg <= 48 * 1024)
-        k_prolong<E, MODE, true><<<grid, 256, stg, s>>>(v, d->phi, d->boff, c, g.V, g.Vh, g.Vbh, d->r, d->Ns, d->Nb,
-                                                        n, nchunk);
-    else
-        k_prolong<E, MODE, false><<<grid, 256, 0, s>>>(v, d->phi, d->boff, c, g.V, g.Vh, g.Vbh, d->r, d->Ns, d->Nb,
-                                                       n, nchunk);
+#define DFL_PROLONG(P)                                                                                            \
+    {                                                                                                             \
+        if (stg <= 48 * 1024)                                                                                     \
+            k_prolong<E, MODE, true, P><<<grid, 256, stg, s>>>(v, d->phi, d->boff, c, g.V, g.Vh, g.Vbh, d->r,     \
+                                                               d->Ns, d->Nb, n, nchunk, ng);                      \
+        else                                                                                                      \
+            k_prolong<E, MODE, false, P><<<grid, 256, 0, s>>>(v, d->phi, d->boff, c, g.V, g.Vh, g.Vbh, d->r,      \
+                                                              d->Ns, d->Nb, n, nchunk, ng);                       \
+    }
+    if (PR == 12) DFL_PROLONG(12)
+    else if (PR == 4) DFL_PROLONG(4)
+    else DFL_PROLONG(1)
+#undef DFL_PROLONG
     DFL_HIP(hipGetLastError());
     return 0;
 }
