@@ -54,7 +54,7 @@ __device__ inline R wave_sum(R v) {
 // lnbr (identical for every block); hops inside a block never cross the
 // lattice boundary, so no boundary sign enters.
 template <class R, int LF, bool ODD>
-__device__ inline void block_hop(const void *U, const short *lnbr, long V, long Vh, long boff, int j, int Vbh,
+__device__ inline void block_hop(const void *U, const short *lnbr, long V, long Vh, long boff, int j, int Vbh, int LS,
                                  const cx<R> *buf, cx<R> acc[12]) {
 #pragma unroll
     for (int k = 0; k < 12; ++k) acc[k] = {R(0), R(0)};
@@ -69,12 +69,12 @@ __device__ inline void block_hop(const void *U, const short *lnbr, long V, long 
         const int lb = (short)(nbw[MU] >> 16);                                          \
         if (lf >= 0) {                                                                  \
             Link<LF>::load(U, V, MU, x, w);                                             \
-            _Pragma("unroll") for (int k = 0; k < 12; ++k) p[k] = buf[k * Vbh + lf];    \
+            _Pragma("unroll") for (int k = 0; k < 12; ++k) p[k] = buf[k * LS + lf];    \
             hop<R, MU, true>(w, p, R(1), acc);                                          \
         }                                                                               \
         if (lb >= 0) {                                                                  \
             Link<LF>::load(U, V, MU, yoff + (unsigned)lb, w);                           \
-            _Pragma("unroll") for (int k = 0; k < 12; ++k) p[k] = buf[k * Vbh + lb];    \
+            _Pragma("unroll") for (int k = 0; k < 12; ++k) p[k] = buf[k * LS + lb];    \
             hop<R, MU, false>(w, p, R(1), acc);                                         \
         }                                                                               \
     }
@@ -233,7 +233,7 @@ struct HalfI<__half> {
 // direction MU at offset fo (the lengths before it).
 template <class SI, class R, int MU>
 __device__ inline void face_absorb(const int *bface, int fcap, int nf, int fo, int nft, int tid, int NT,
-                                   const void *fx, int qr, long nfx, long B, int Vbh, R kappa, cx<R> *Rb,
+                                   const void *fx, int qr, long nfx, long B, int LS, R kappa, cx<R> *Rb,
                                    cx<R> *Tb) {
     for (int k = tid; k < nf; k += NT) {
         const int ent = bface[MU * fcap + k];
@@ -242,13 +242,13 @@ __device__ inline void face_absorb(const int *bface, int fcap, int nf, int fo, i
         HalfI<SI>::load(fx, nfx, (unsigned)(B * nft + fo + k), qr, g);
         cx<R> *buf = par ? Tb : Rb;
 #pragma unroll
-        for (int c = 0; c < 12; ++c) a[c] = buf[c * Vbh + j];
+        for (int c = 0; c < 12; ++c) a[c] = buf[c * LS + j];
         if (!bwd)
             reconstruct_add<R, MU, -1>(g, kappa, a);
         else
             reconstruct_add<R, MU, +1>(g, kappa, a);
 #pragma unroll
-        for (int c = 0; c < 12; ++c) buf[c * Vbh + j] = a[c];
+        for (int c = 0; c < 12; ++c) buf[c * LS + j] = a[c];
     }
 }
 
@@ -257,7 +257,7 @@ __device__ inline void face_absorb(const int *bface, int fcap, int nf, int fo, i
 template <class SI, class R, int LF, int MU>
 __device__ inline void face_emit(const int *bface, const int *bfsrc, const int *bfnb, int fcap, int nf, int fo,
                                  int nft, int tid, int NT, const void *U, void *fx, int qr, long nfx, long V,
-                                 long Vh, long B, int Vbh, const cx<R> *De, const cx<R> *Do) {
+                                 long Vh, long B, int Vbh, int LS, const cx<R> *De, const cx<R> *Do) {
     for (int k = tid; k < nf; k += NT) {
         const int ent = bface[MU * fcap + k], src = bfsrc[MU * fcap + k];
         const int par = ent >> 30, bwd = (ent >> 29) & 1, j = ent & 0x1fffffff;
@@ -267,7 +267,7 @@ __device__ inline void face_emit(const int *bface, const int *bfsrc, const int *
         const cx<R> *buf = py ? Do : De;
         cx<R> d[12], h[6], g[6], w[9];
 #pragma unroll
-        for (int c = 0; c < 12; ++c) d[c] = buf[c * Vbh + jy];
+        for (int c = 0; c < 12; ++c) d[c] = buf[c * LS + jy];
         if (!bwd) {
             Link<LF>::load(U, V, MU, (unsigned)(par * Vh + Rblk * Vbh + j), w);
             project<R, MU, -1>(d, h);
@@ -289,7 +289,8 @@ enum SweepFlags { SW_FIRST = 1, SW_FACES = 2, SW_STORE_RES = 4, SW_EMIT = 8 };
 
 // VBHC > 0: the block's sites per parity as a compile-time constant (the
 // component planes of the exchange buffers then sit at immediate LDS
-// offsets); 0: taken from the argument.
+// offsets); 0: taken from the argument; < 0: taken from the argument, with the
+// planes of the exchange buffers -VBHC apart.
 // NR = 2 (FP32 vectors in LDS, KS = 1): a workgroup takes two right-hand
 // sides of its block, each wave 64 / NR sites for both, so the two lanes of
 // a site read the same links and clover entries in one instruction.  Every
@@ -310,6 +311,7 @@ __global__ void __launch_bounds__(MAXT, (sizeof(R) == 4 && LF >= LNK_F16 && LDS 
     static_assert(NR == 1 || (LDS && KS == 1 && Spin<S>::NCH * 16 == Spin<S>::BYTES), "NR = 2 layout");
     constexpr int SPW = 64 / NR;   // sites per wave
     const int Vbh = VBHC > 0 ? VBHC : Vbh_arg;
+    const int LS = VBHC < 0 ? -VBHC : Vbh;   // stride of the exchange buffers' component planes
     extern __shared__ unsigned char dsm[];
     __shared__ R red[16][NR][3];
     const int lane = threadIdx.x & 63, qr = NR > 1 ? lane / SPW : 0;   // this lane's right-hand side
@@ -332,11 +334,11 @@ __global__ void __launch_bounds__(MAXT, (sizeof(R) == 4 && LF >= LNK_F16 && LDS 
     const long boff = B * Vbh;
     cx<R> *Rb, *Tb;
     if (LDS) {
-        Rb = reinterpret_cast<cx<R> *>(dsm) + (size_t)qr * 24 * Vbh;
+        Rb = reinterpret_cast<cx<R> *>(dsm) + (size_t)qr * 24 * LS;
     } else {
-        Rb = gbuf + ((size_t)rhs * gridDim.x + bx) * (size_t)24 * Vbh;
+        Rb = gbuf + ((size_t)rhs * gridDim.x + bx) * (size_t)24 * LS;
     }
-    Tb = Rb + 12 * Vbh;
+    Tb = Rb + 12 * LS;
 
     cx<R> xe[KS][12];
     // ---- block residual: eta (first cycle) or the stored residual, then the
@@ -352,24 +354,24 @@ __global__ void __launch_bounds__(MAXT, (sizeof(R) == 4 && LF >= LNK_F16 && LDS 
             else
                 VecI<SI>::load(res, V, xe_i, qr, e);
 #pragma unroll
-            for (int c = 0; c < 12; ++c) Rb[c * Vbh + j] = e[c];
+            for (int c = 0; c < 12; ++c) Rb[c * LS + j] = e[c];
             if (first)
                 Spin<S>::load(eta, V, xo_i + qoff, e);
             else
                 VecI<SI>::load(res, V, xo_i, qr, e);
 #pragma unroll
-            for (int c = 0; c < 12; ++c) Tb[c * Vbh + j] = e[c];
+            for (int c = 0; c < 12; ++c) Tb[c * LS + j] = e[c];
         }
     }
     if (flags & SW_FACES) {
         __syncthreads();
-        face_absorb<SI, R, 0>(bface, fcap, nface.x, 0, nft, tid, NT, fx, qr, nfx, B, Vbh, kappa, Rb, Tb);
+        face_absorb<SI, R, 0>(bface, fcap, nface.x, 0, nft, tid, NT, fx, qr, nfx, B, LS, kappa, Rb, Tb);
         __syncthreads();
-        face_absorb<SI, R, 1>(bface, fcap, nface.y, fo1, nft, tid, NT, fx, qr, nfx, B, Vbh, kappa, Rb, Tb);
+        face_absorb<SI, R, 1>(bface, fcap, nface.y, fo1, nft, tid, NT, fx, qr, nfx, B, LS, kappa, Rb, Tb);
         __syncthreads();
-        face_absorb<SI, R, 2>(bface, fcap, nface.z, fo2, nft, tid, NT, fx, qr, nfx, B, Vbh, kappa, Rb, Tb);
+        face_absorb<SI, R, 2>(bface, fcap, nface.z, fo2, nft, tid, NT, fx, qr, nfx, B, LS, kappa, Rb, Tb);
         __syncthreads();
-        face_absorb<SI, R, 3>(bface, fcap, nface.w, fo3, nft, tid, NT, fx, qr, nfx, B, Vbh, kappa, Rb, Tb);
+        face_absorb<SI, R, 3>(bface, fcap, nface.w, fo3, nft, tid, NT, fx, qr, nfx, B, LS, kappa, Rb, Tb);
         __syncthreads();
     }
     // ---- s_o = A_oo^{-1} rho_o into T; rho_o is parked in the residual
@@ -380,11 +382,11 @@ __global__ void __launch_bounds__(MAXT, (sizeof(R) == 4 && LF >= LNK_F16 && LDS 
         if (j < Vbh) {
             cx<R> e[12], m[12];
 #pragma unroll
-            for (int c = 0; c < 12; ++c) e[c] = Tb[c * Vbh + j];
+            for (int c = 0; c < 12; ++c) e[c] = Tb[c * LS + j];
             VecI<SI>::store(res, V, Vh + boff + j, qr, e);
             clover_apply<CF>(cinv, Vh, boff + j, e, m);
 #pragma unroll
-            for (int c = 0; c < 12; ++c) Tb[c * Vbh + j] = m[c];
+            for (int c = 0; c < 12; ++c) Tb[c * LS + j] = m[c];
         }
     }
     __syncthreads();
@@ -394,10 +396,10 @@ __global__ void __launch_bounds__(MAXT, (sizeof(R) == 4 && LF >= LNK_F16 && LDS 
         const int j = tid + k * NT;
         if (j < Vbh) {
             cx<R> acc[12];
-            block_hop<R, LF, false>(U, lnbr, V, Vh, boff, j, Vbh, Tb, acc);
+            block_hop<R, LF, false>(U, lnbr, V, Vh, boff, j, Vbh, LS, Tb, acc);
 #pragma unroll
             for (int c = 0; c < 12; ++c) {
-                Rb[c * Vbh + j] = rmac(Rb[c * Vbh + j], kappa, acc[c]);
+                Rb[c * LS + j] = rmac(Rb[c * LS + j], kappa, acc[c]);
                 xe[k][c] = {R(0), R(0)};
             }
         }
@@ -411,10 +413,10 @@ __global__ void __launch_bounds__(MAXT, (sizeof(R) == 4 && LF >= LNK_F16 && LDS 
             const int j = tid + k * NT;
             if (j < Vbh) {
                 cx<R> acc[12], t[12];
-                block_hop<R, LF, true>(U, lnbr, V, Vh, boff, j, Vbh, Rb, acc);
+                block_hop<R, LF, true>(U, lnbr, V, Vh, boff, j, Vbh, LS, Rb, acc);
                 clover_apply<CF>(cinv, Vh, boff + j, acc, t);
 #pragma unroll
-                for (int c = 0; c < 12; ++c) Tb[c * Vbh + j] = t[c];
+                for (int c = 0; c < 12; ++c) Tb[c * LS + j] = t[c];
             }
         }
         __syncthreads();
@@ -425,11 +427,18 @@ __global__ void __launch_bounds__(MAXT, (sizeof(R) == 4 && LF >= LNK_F16 && LDS 
         for (int k = 0; k < KS; ++k) {
             const int j = tid + k * NT;
             if (j < Vbh) {
+                // hops first and the clover term's loads held back until they are
+                // done: the other way round A_ee r is carried through the hops
+                // and the sweeps need 24 to 60 registers more (spills where the
+                // occupancy asks for 168).  24^3 x 48, 24 rhs, 10 sweeps: FP32
+                // 24.9 -> 21.1 ms (two waves per SIMD -> three), FP16 21.7 ->
+                // 19.8; 6^4 blocks, 6 rhs, BF16 6.3 -> 6.05
                 cx<R> acc[12], r[12];
+                block_hop<R, LF, false>(U, lnbr, V, Vh, boff, j, Vbh, LS, Tb, acc);
+                asm volatile("" ::: "memory");
 #pragma unroll
-                for (int c = 0; c < 12; ++c) r[c] = Rb[c * Vbh + j];
+                for (int c = 0; c < 12; ++c) r[c] = Rb[c * LS + j];
                 clover_apply<CF>(clo, V, boff + j, r, p[k]);
-                block_hop<R, LF, false>(U, lnbr, V, Vh, boff, j, Vbh, Tb, acc);
 #pragma unroll
                 for (int c = 0; c < 12; ++c) {
                     p[k][c] = rmac(p[k][c], -k2, acc[c]);
@@ -467,14 +476,14 @@ __global__ void __launch_bounds__(MAXT, (sizeof(R) == 4 && LF >= LNK_F16 && LDS 
                     // the block's residual after the update: the new r on even sites
                     cx<R> rn[12];
 #pragma unroll
-                    for (int c = 0; c < 12; ++c) rn[c] = cmac(Rb[c * Vbh + j], -alpha, p[k][c]);
+                    for (int c = 0; c < 12; ++c) rn[c] = cmac(Rb[c * LS + j], -alpha, p[k][c]);
                     VecI<SI>::store(res, V, boff + j, qr, rn);
                 }
 #pragma unroll
                 for (int c = 0; c < 12; ++c) {
-                    const cx<R> rc = Rb[c * Vbh + j];
+                    const cx<R> rc = Rb[c * LS + j];
                     xe[k][c] = cmac(xe[k][c], alpha, rc);
-                    Rb[c * Vbh + j] = last ? xe[k][c] : cmac(rc, -alpha, p[k][c]);
+                    Rb[c * LS + j] = last ? xe[k][c] : cmac(rc, -alpha, p[k][c]);
                 }
             }
         }
@@ -489,8 +498,8 @@ __global__ void __launch_bounds__(MAXT, (sizeof(R) == 4 && LF >= LNK_F16 && LDS 
                 cx<R> rn[12];
 #pragma unroll
                 for (int c = 0; c < 12; ++c) {
-                    rn[c] = Rb[c * Vbh + j];
-                    Rb[c * Vbh + j] = {R(0), R(0)};
+                    rn[c] = Rb[c * LS + j];
+                    Rb[c * LS + j] = {R(0), R(0)};
                 }
                 if (flags & SW_STORE_RES) VecI<SI>::store(res, V, boff + j, qr, rn);
             }
@@ -507,7 +516,7 @@ __global__ void __launch_bounds__(MAXT, (sizeof(R) == 4 && LF >= LNK_F16 && LDS 
         if (j < Vbh) {
             const long xe_i = boff + j, xo_i = Vh + boff + j;
             cx<R> acc[12], t[12], q[12];
-            block_hop<R, LF, true>(U, lnbr, V, Vh, boff, j, Vbh, Rb, acc);
+            block_hop<R, LF, true>(U, lnbr, V, Vh, boff, j, Vbh, LS, Rb, acc);
             VecI<SI>::load(res, V, xo_i, qr, t);
 #pragma unroll
             for (int c = 0; c < 12; ++c) acc[c] = rmac(t[c], kappa, acc[c]);   // u_o
@@ -515,7 +524,7 @@ __global__ void __launch_bounds__(MAXT, (sizeof(R) == 4 && LF >= LNK_F16 && LDS 
             if (flags & SW_EMIT) {
                 // delta_o for the face exchange (T is free: only R = x_e is read here)
 #pragma unroll
-                for (int c = 0; c < 12; ++c) Tb[c * Vbh + j] = q[c];
+                for (int c = 0; c < 12; ++c) Tb[c * LS + j] = q[c];
             }
             if (flags & SW_STORE_RES) {
                 // odd residual u_o - A_oo delta_o: zero up to rounding when the
@@ -548,13 +557,13 @@ __global__ void __launch_bounds__(MAXT, (sizeof(R) == 4 && LF >= LNK_F16 && LDS 
     }
     if (flags & SW_EMIT) {
         __syncthreads();
-        face_emit<SI, R, LF, 0>(bface, bfsrc, bfnb, fcap, nface.x, 0, nft, tid, NT, U, fx, qr, nfx, V, Vh, B, Vbh, Rb,
+        face_emit<SI, R, LF, 0>(bface, bfsrc, bfnb, fcap, nface.x, 0, nft, tid, NT, U, fx, qr, nfx, V, Vh, B, Vbh, LS, Rb,
                                Tb);
-        face_emit<SI, R, LF, 1>(bface, bfsrc, bfnb, fcap, nface.y, fo1, nft, tid, NT, U, fx, qr, nfx, V, Vh, B, Vbh,
+        face_emit<SI, R, LF, 1>(bface, bfsrc, bfnb, fcap, nface.y, fo1, nft, tid, NT, U, fx, qr, nfx, V, Vh, B, Vbh, LS,
                                Rb, Tb);
-        face_emit<SI, R, LF, 2>(bface, bfsrc, bfnb, fcap, nface.z, fo2, nft, tid, NT, U, fx, qr, nfx, V, Vh, B, Vbh,
+        face_emit<SI, R, LF, 2>(bface, bfsrc, bfnb, fcap, nface.z, fo2, nft, tid, NT, U, fx, qr, nfx, V, Vh, B, Vbh, LS,
                                Rb, Tb);
-        face_emit<SI, R, LF, 3>(bface, bfsrc, bfnb, fcap, nface.w, fo3, nft, tid, NT, U, fx, qr, nfx, V, Vh, B, Vbh,
+        face_emit<SI, R, LF, 3>(bface, bfsrc, bfnb, fcap, nface.w, fo3, nft, tid, NT, U, fx, qr, nfx, V, Vh, B, Vbh, LS,
                                Rb, Tb);
     }
 }
@@ -636,7 +645,7 @@ static int run_sap(qcd_field f, int ncy, int nmr, const void *eta, void *psi, in
 #define DFL_SAP_LAUNCH(LDSV, KSV, MAXT, VBHC)                                                                  \
     {                                                                                                          \
         auto kern = k_sap_sweep<S, R, LF, CF, LDSV, KSV, MAXT, VBHC, 1, SI>;                                   \
-        size_t sh = LDSV ? lds : 0;                                                                            \
+        size_t sh = LDSV ? (VBHC < 0 ? lds / Vbh * -VBHC : lds) : 0;                                                                            \
         if (LDSV && sh > 64 * 1024) (void)hipFuncSetAttribute((const void *)kern,                              \
                                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh); \
         kern<<<grid, NT, sh, s>>>(DFL_SAP_ARGS);                                                               \
@@ -655,7 +664,22 @@ static int run_sap(qcd_field f, int ncy, int nmr, const void *eta, void *psi, in
                 else if (NT <= 256) DFL_SAP_LAUNCH(true, 1, 256, 0)
                 // a bound of 768 threads (e.g. 6^4 blocks, 704) leaves 168
                 // registers per lane where 1024 would cap them at 128
-                else if (NT <= 768) DFL_SAP_LAUNCH(true, 1, 768, 0)
+                else if (NT <= 768) {
+                    // where one workgroup fills the LDS anyway, its component
+                    // planes take a fixed stride, so that they sit at immediate
+                    // offsets (16 bits: 11 planes of 744 complex at most) as with
+                    // the compile-time block sizes.  Addresses in registers made
+                    // the sweep spill: 6^4 blocks, 24^3 x 48, BF16, 6 rhs, 10
+                    // sweeps 11.8 -> 6.3 ms.  Up to 384 sites two workgroups
+                    // share the LDS and the exact stride stays
+                    if constexpr (sizeof(R) == 4) {
+                        if (NT > 384 && Vbh <= 744) {
+                            DFL_SAP_LAUNCH(true, 1, 768, -744)
+                            continue;
+                        }
+                    }
+                    DFL_SAP_LAUNCH(true, 1, 768, 0)
+                }
                 else DFL_SAP_LAUNCH(true, 1, 1024, 0)
             } else {
                 if (KS == 1) DFL_SAP_LAUNCH(false, 1, 1024, 0)
