@@ -444,7 +444,7 @@ int little_fold(qcd_dfl d, double2 *work, hipStream_t s) {
 // system (x_O is exact given x_E); it is reported relative to ||u||.  poll: stop
 // when every right-hand side is at tol (at most maxit iterations, restarted
 // every 24); otherwise run one cycle of min(maxit, 24) iterations without host
-// synchronisation.
+// synchronisation.  No iterations (maxit <= 0): x_O = A_OO^{-1} u_O, x_E = 0.
 int little_solve(qcd_dfl d, const double2 *u, double2 *x, int n, double tol, int maxit, bool poll, int *iters_out,
                  double *relres_out, hipStream_t s) {
     // polled norms pass through the handle's pinned buffer of 4096 doubles
@@ -492,6 +492,13 @@ int little_solve(qcd_dfl d, const double2 *u, double2 *x, int n, double tol, int
     int iters = 0;
     double worst = 0;
     bool done = false, first = true;
+    // y = the combination of k residuals (the first time), += it (after a restart)
+    auto accum = [&](int k) -> int {
+        k_little_accum<<<dim3(nblocks(ne, LB), n), LB, 0, s>>>(y, Rv, ne, n, k, Rm, cvec, first ? 1 : 0);
+        DFL_HIP(hipGetLastError());
+        first = false;
+        return 0;
+    };
     while (!done && iters < maxit) {
         int k = 0;
         while (!done && k < nkv && iters < maxit) {
@@ -529,9 +536,7 @@ int little_solve(qcd_dfl d, const double2 *u, double2 *x, int n, double tol, int
                 }
             }
         }
-        k_little_accum<<<dim3(nblocks(ne, LB), n), LB, 0, s>>>(y, Rv, ne, n, k, Rm, cvec, first ? 1 : 0);
-        DFL_HIP(hipGetLastError());
-        first = false;
+        DFL_TRY(accum(k));
         if (!poll) break;
         if (!done && iters < maxit) {   // restart from the true residual u' - (y - A_EO M1 y)
             DFL_TRY(rows(Rows{d->M1, nullptr, 8, 0, 8, y, o_nb, nh, nullptr, nullptr, 0, q, nullptr, nh, 1.0}));
@@ -540,6 +545,7 @@ int little_solve(qcd_dfl d, const double2 *u, double2 *x, int n, double tol, int
             DFL_HIP(hipGetLastError());
         }
     }
+    if (first) DFL_TRY(accum(0));   // no steps (maxit <= 0): y = 0, x_E = 0 and x_O = g_O
     // x_O = g_O - M1 y, x_E = A_EE^{-1} y
     DFL_TRY(rows(Rows{d->M1, nullptr, 8, 0, 8, y, o_nb, nh, g, nullptr, nh, x, orow, Nb, -1.0}));
     DFL_TRY(rows(Rows{d->Dinv, erow, 1, 0, 1, y, nullptr, nh, nullptr, nullptr, 0, x, erow, Nb, 1.0}));

@@ -1,0 +1,71 @@
+"""Deflated solves whose little solve takes no step (a little_maxit of zero, what a
+zero-initialised parameter struct holds, or below): the little inverse is then that
+of the odd blocks alone, x_O = A_OO^{-1} u_O and x_E = 0, whatever the handle's
+work space holds from calls before.
+
+One outer step is put together from the public operators: the low-mode part x0 of
+b, z = M_SAP r - Phi A0 Phi^+ M M_SAP r with r = b - M x0, and x = x0 + z (w, r) / (w, w)
+with w = M z.  All in FP64; the low-mode part is solved to 1e-12 on both sides and
+the rest is some hundred roundings, so 1e-9 of the norm leaves room for a condition
+number of 1e3."""
+
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+DIMS, BLOCK = (16, 8, 8, 8), (4, 4, 4, 4)
+
+
+def odd_blocks(dims, block):
+    """Lexicographic deflation blocks whose coordinates have an odd sum."""
+    nb = [L // b for L, b in zip(dims, block)]
+    out = []
+    for B in range(nb[0] * nb[1] * nb[2] * nb[3]):
+        q, tot = B, 0
+        for m in (3, 2, 1, 0):
+            tot += q % nb[m]
+            q //= nb[m]
+        if tot % 2:
+            out.append(B)
+    return out
+
+
+@pytest.mark.parametrize("maxit", [0, -1])
+def test_solve_without_little_steps(maxit):
+    import torch
+    import paper_1605_00564_amd as dfl
+    fld = dfl.Field(DIMS, BLOCK, 0.124, 1.5, synth.gauge_field(DIMS, 0.4, 1))
+    d = dfl.Deflation(fld, Ns=6, ninv=3, seed=11)
+    n, sap = 2, dfl.SapParams(5, 4, dfl.F64)
+    b = torch.from_numpy(synth.gaussian_spinor(DIMS, n, 5001)).cuda()
+    odd = torch.tensor(odd_blocks(DIMS, BLOCK), device="cuda")
+    # A_OO: odd blocks couple to even ones only
+    aoo = torch.empty((len(odd), d.Ns, d.Ns), dtype=torch.complex128, device="cuda")
+    for l in range(d.Ns):
+        e = torch.zeros((1, d.Nb, d.Ns), dtype=torch.complex128, device="cuda")
+        e[0, odd, l] = 1
+        aoo[:, :, l] = d.little_apply(e)[0, odd]
+
+    x0 = d.prolong(d.little_solve(d.restrict(b), tol=1e-12)[0])
+    r = b - dfl.dirac_apply(fld, x0)
+    z = dfl.sap_precond(fld, r, sap)
+    u = d.restrict(dfl.dirac_apply(fld, z))
+    c = torch.zeros_like(u)
+    c[:, odd] = torch.linalg.solve(aoo.cpu(), u[:, odd].permute(1, 2, 0).contiguous().cpu()).permute(2, 0, 1).cuda()
+    z = z - d.prolong(c)
+    w = dfl.dirac_apply(fld, z)
+    ref = torch.empty_like(b)
+    for i in range(n):
+        ref[i] = x0[i] + z[i] * (torch.vdot(w[i].flatten(), r[i].flatten()) / (w[i].norm() ** 2))
+
+    p = dfl.GcrParams(nkv=1, fixed_iters=1, res=1e-3, sap=sap, dfl=d, little_tol=1e-12, little_maxit=maxit)
+    junk = torch.randn((n, d.Nb, d.Ns), dtype=torch.complex128, device="cuda")
+    for scale in (1.0, 1e6):
+        d.little_solve(scale * junk, tol=1e-13)      # leaves its Krylov vectors in the work space
+        x = dfl.gcr_solve(fld, b, p)[0]
+        for i in range(n):
+            assert float((x[i] - ref[i]).norm() / ref[i].norm()) <= 1e-9, (scale, i)
+    d.close()
+    fld.close()
