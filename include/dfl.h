@@ -177,6 +177,9 @@ typedef struct {
     double ref_res;        /* relative residual of those solves, in (0, 1) */
 } qcd_dfl_params;
 
+/* deflation_setup and deflation_set_phi wait for their stream: the handle they
+ * leave is complete on return and may be used on any stream (one at a time:
+ * calls on a handle share its work space). */
 int deflation_setup(qcd_field f, const qcd_dfl_params *p, hipStream_t stream, qcd_dfl *out);
 int deflation_destroy(qcd_dfl d);
 /* Deflation fields as complex128 DEVICE buffer [Nb][Ns][Vb][4][3]: deflation

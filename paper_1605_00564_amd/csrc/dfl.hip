@@ -700,11 +700,13 @@ int build_little(qcd_dfl d, hipStream_t s) {
     DFL_HIP(hipMemsetAsync(f->flag, 0, sizeof(int), s));
     k_block_inverse<<<nblocks(Nb, 64), 64, 0, s>>>(d->A, d->Dinv, work, Nb, Ns, f->flag);
     DFL_HIP(hipGetLastError());
+    DFL_TRY(little_fold(d, work, s));   // of no use if a block is singular
+    // the last wait: the handle is complete on return, for every stream
     int flag = 0;
     DFL_HIP(hipMemcpyAsync(&flag, f->flag, sizeof(int), hipMemcpyDeviceToHost, s));
     DFL_HIP(hipStreamSynchronize(s));
     if (flag) return set_error(QCD_ESINGULAR, "a diagonal block of the little operator is singular");
-    return little_fold(d, work, s);
+    return 0;
 }
 
 void dfl_free(qcd_dfl d) {
