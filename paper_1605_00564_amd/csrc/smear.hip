@@ -422,26 +422,30 @@ extern "C" int qcd_field_ape_smear(qcd_field f, double alpha, int n_iter, hipStr
     if (!f || n_iter < 0 || !std::isfinite(alpha)) return set_error(QCD_EINVAL, "bad arguments to qcd_field_ape_smear");
     const long V = f->g.V;
     const size_t bytes = sizeof(double2) * 27 * (size_t)V;
-    if (!f->Uape && !dev_alloc(f->device, (void **)&f->Uape, bytes))
+    // the scratch first, and new links reach the handle once they are on their
+    // way: a call that fails leaves what it had (links, or none)
+    void *w = nullptr, *links = f->Uape;
+    if (n_iter > 0) DFL_TRY(field_buffer(f, BUF_APPLY, bytes, &w));
+    if (!links && !dev_alloc(f->device, &links, bytes))
         return set_error(QCD_ENOMEM, "device allocation of the smeared links failed");
     // spatial links of the FP64 copy, then n_iter steps ping-ponging through
     // the handle's scratch, so that the last one lands in the kept links
     const double2 *U64 = static_cast<const double2 *>(f->U[LNK_F64]);
     const Box box{f->g.L[1], f->g.L[2], f->g.L[3]};
-    double2 *a = static_cast<double2 *>(f->Uape), *b = nullptr;
-    if (n_iter > 0) {
-        void *w;
-        DFL_TRY(field_buffer(f, BUF_APPLY, bytes, &w));
-        b = static_cast<double2 *>(w);
-        if (n_iter % 2) std::swap(a, b);
-    }
+    double2 *a = static_cast<double2 *>(links), *b = static_cast<double2 *>(w);
+    if (n_iter % 2) std::swap(a, b);
     ProfScope ps(PROF_OTHER, s);
     k_ape_import<<<(unsigned)(V / 256), 256, 0, s>>>(U64, a, f->int_of, V);
     for (int it = 0; it < n_iter; ++it) {
         k_ape_step<<<dim3(nblocks(V, 128), 3), 128, 0, s>>>(a, b, box, V, alpha);
         std::swap(a, b);
     }
-    DFL_HIP(hipGetLastError());
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) {
+        if (!f->Uape) (void)hipFree(links);
+        return set_error(QCD_EHIP, std::string("APE smearing: ") + hipGetErrorString(e));
+    }
+    f->Uape = links;
     return 0;
 }
 
