@@ -427,10 +427,9 @@ int gauss_smear(qcd_field f, const void *in, void *out, int nrhs, qcd_prec io, d
 
 /* Launch choices of a handle's Dirac stencil and Schwarz sweeps, for the
  * autotuner (defaults: block-staged, automatic, lexicographic, automatic,
- * 1, 1).  The stencil choices speak of the kernels on the internal layout,
- * which the solvers use; with all of them at their defaults, dirac_apply on
- * 16-byte aligned vectors of the operator's own vector type runs on the
- * canonical vectors directly:
+ * 1, 1, 0).  The stencil choices speak of the kernels on the internal layout,
+ * which the solvers use; whether dirac_apply uses them too is the last knob's
+ * choice:
  * QCD_TUNE_STENCIL_BLOCK  1 = one workgroup per Schwarz block with the
  *                         block's spinors staged in LDS (when it fits),
  *                         0 = site tiles;
@@ -453,7 +452,15 @@ int gauss_smear(qcd_field f, const void *in, void *out, int nrhs, qcd_prec io, d
  *                         right-hand sides: 1 = two right-hand sides per
  *                         workgroup, sharing link and clover loads (the
  *                         block reductions then add in another order), 0 =
- *                         one.
+ *                         one;
+ * QCD_TUNE_DIRAC_CANON    dirac_apply on 16-byte aligned, non-overlapping
+ *                         vectors of the operator's own vector type:
+ *                         1 = on the canonical vectors themselves, with no
+ *                         conversions, 2 = converted to the internal layout
+ *                         and back around the stencil that the other knobs
+ *                         choose, 0 = as 1 while every stencil knob has its
+ *                         default, else as 2.  An autotuner sets 2 while it
+ *                         compares stencils and 1 when it is done.
  * Results do not depend on these beyond rounding; graphs captured on the
  * handle are dropped.  Unknown knob or value: QCD_EINVAL. */
 #define QCD_TUNE_STENCIL_BLOCK 0
@@ -462,6 +469,7 @@ int gauss_smear(qcd_field f, const void *in, void *out, int nrhs, qcd_prec io, d
 #define QCD_TUNE_STENCIL_NR 3
 #define QCD_TUNE_STENCIL_LINKLDS 4
 #define QCD_TUNE_SAP_PAIR 5
+#define QCD_TUNE_DIRAC_CANON 6
 int qcd_field_tune(qcd_field f, int knob, int value);
 
 /* Process-wide workspace cache.  Scratch buffers that a handle gives up

@@ -240,6 +240,7 @@ class Field:
 
     TUNE_STENCIL_BLOCK, TUNE_STENCIL_RG, TUNE_STENCIL_ORDER, TUNE_STENCIL_NR, TUNE_STENCIL_LINKLDS = 0, 1, 2, 3, 4
     TUNE_SAP_PAIR = 5
+    TUNE_DIRAC_CANON = 6
 
     def tune(self, knob: int, value: int):
         """Set a launch choice of the Dirac stencil (see include/dfl.h)."""

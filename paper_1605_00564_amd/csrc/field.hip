@@ -560,6 +560,11 @@ int qcd_field_tune(qcd_field f, int knob, int value) {
                 return set_error(QCD_EINVAL, "right-hand sides per block workgroup must be 0, 1, 2 or 4");
             f->st_nr = value;
             break;
+        case QCD_TUNE_DIRAC_CANON:
+            if (value < 0 || value > 2)
+                return set_error(QCD_EINVAL, "the canonical-vector choice must be 0, 1 or 2");
+            f->st_canon = value;
+            break;
         default: return set_error(QCD_EINVAL, "unknown tuning knob");
     }
     ++f->graph_gen;   // captured graphs hold the previous launch choices

@@ -1,0 +1,61 @@
+"""The operator on canonical vectors after the autotuner has chosen a stencil for the
+solver: a tuned handle still takes the kernel that needs no conversions, and the
+knob that decides it.  Which way a call went shows in the handle's work space:
+converted vectors are kept there, canonical ones need none."""
+
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+DIMS, BLOCK = (16, 8, 8, 8), (4, 4, 4, 4)
+
+
+def _handle():
+    import torch
+    import paper_1605_00564_amd as dfl
+    fld = dfl.Field(DIMS, BLOCK, 0.124, 1.5, synth.gauge_field(DIMS, 0.4, 1))
+    g = torch.Generator(device="cuda").manual_seed(4)
+    x = torch.randn((4, fld.V, 4, 3), dtype=torch.complex64, device="cuda", generator=g)
+    return torch, dfl, fld, x
+
+
+def _converted(dfl, fld, x, storage):
+    """Whether a call took work space, and its result."""
+    fld.trim()
+    dfl.workspace_trim()
+    y = dfl.dirac_apply(fld, x, storage=storage)
+    fld.trim()
+    return dfl.workspace_cached(0) > 0, y
+
+
+@pytest.mark.parametrize("storage", [1, 2])
+def test_tuned_handle_keeps_the_canonical_operator(storage):
+    torch, dfl, fld, x = _handle()
+    from paper_1605_00564_amd import tune
+    conv, y = _converted(dfl, fld, x, storage)
+    assert not conv
+    best, times = tune.tune_stencil(fld, 4, storage=storage, reps=1)
+    assert best in times and len(times) == 7
+    conv, z = _converted(dfl, fld, x, storage)
+    assert not conv and torch.equal(z, y)
+    fld.close()
+
+
+def test_canonical_knob():
+    torch, dfl, fld, x = _handle()
+    F = dfl.Field
+    ref = dfl.dirac_apply(fld, x, storage=1)
+    for order, canon, expect in ((1, 0, False), (1, 1, False), (1, 2, True),
+                                 (0, 0, True), (0, 1, False), (0, 2, True)):
+        fld.tune(F.TUNE_STENCIL_ORDER, order)           # 0 is not the default
+        fld.tune(F.TUNE_DIRAC_CANON, canon)
+        conv, y = _converted(dfl, fld, x, 1)
+        assert conv == expect, (order, canon)
+        assert float((y - ref).norm() / ref.norm()) < 1e-6
+    for value in (-1, 3):
+        with pytest.raises(dfl.DflError) as e:
+            fld.tune(F.TUNE_DIRAC_CANON, value)
+        assert e.value.code == -1
+    fld.close()
