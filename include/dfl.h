@@ -123,8 +123,9 @@ int dirac_apply_ex(qcd_field f, const void *in, void *out, int nrhs, qcd_prec io
  * (held from the library's first use of that GPU until the process ends)
  * instead of workspace that grows on demand; no device memory is allocated
  * and no profiling events are created.  Staging needs 2 x nrhs x V x 96
- * bytes (FP32 vectors; 192 with FP64 storage); a call that needs more than
- * 64 MiB returns QCD_EINVAL.  Calls overlapping in time on one GPU share the
+ * bytes (FP32 vectors; 192 with FP64 storage); a call for which that is more
+ * than 64 MiB returns QCD_EINVAL, also where nothing would be staged: what is
+ * accepted does not depend on addresses or launch choices.  Calls overlapping in time on one GPU share the
  * array and must not be issued (they race).  The field's device must be
  * current. */
 int dirac_apply_noalloc(qcd_field f, const void *in, void *out, int nrhs, qcd_prec io, qcd_prec storage,

@@ -3,9 +3,9 @@
 //
 // Where dirac_apply stages its input and output in the library's internal
 // layout, it does so in workspace buffers that grow on demand.  This variant
-// stages them in a fixed device array instead: `scratch`, of SCRATCH_BYTES, one copy per GPU,
-// held from the first time the library runs on that GPU until the process
-// ends.  The array's name is a host-side stand-in in host code; its device
+// stages them in a fixed device array instead: `scratch`, of SCRATCH_BYTES, one
+// copy per GPU, held from the first time the library runs on that GPU until the
+// process ends.  The array's name is a host-side stand-in in host code; its device
 // address is looked up once per device (hipGetSymbolAddress, with that
 // device current) and only that address is handed to kernels.  Each call
 // overwrites the whole staging area it uses (the packing kernel writes
@@ -65,6 +65,8 @@ extern "C" int dirac_apply_noalloc(qcd_field f, const void *in, void *out, int n
     if (storage != QCD_F64 && storage != QCD_F32 && storage != QCD_F16 && storage != QCD_BF16)
         return set_error(QCD_EINVAL, "bad operator storage");
     const qcd_prec vec = storage == QCD_F64 ? QCD_F64 : QCD_F32;
+    // the limit holds for every call, whether it stages or not: what is accepted
+    // does not depend on addresses or launch choices
     const size_t nb = spinor_bytes(vec, f->g.V) * (size_t)nrhs;
     if (2 * nb > SCRATCH_BYTES)
         return set_error(QCD_EINVAL, "dirac_apply_noalloc: " + std::to_string(nrhs) + " right-hand sides need " +
