@@ -24,6 +24,7 @@
 
 #include "blas.h"
 #include "dflint.h"
+#include "little_rules.h"
 
 namespace dfl {
 
@@ -418,10 +419,6 @@ __global__ void k_little_minus(const double2 *__restrict__ a, const double2 *__r
     if (i < n) c[i] = make_double2(a[i].x - b[i].x, a[i].y - b[i].y);
 }
 
-// iterations between the host's looks at the norms: a look costs about 12 us, an
-// iteration 30
-constexpr int LOOK = 4;
-
 }  // namespace
 
 int little_apply_dev(qcd_dfl d, const double2 *v, double2 *w, int n, hipStream_t s) {
@@ -492,6 +489,7 @@ int little_solve(qcd_dfl d, const double2 *u, double2 *x, int n, double tol, int
     int iters = 0;
     double worst = 0;
     bool done = false, first = true;
+    int at = 0, want = std::min(look, first_look(tol));   // steps since the last look, until the next one
     // y = the combination of k residuals (the first time), += it (after a restart)
     auto accum = [&](int k) -> int {
         k_little_accum<<<dim3(nblocks(ne, LB), n), LB, 0, s>>>(y, Rv, ne, n, k, Rm, cvec, first ? 1 : 0);
@@ -506,8 +504,7 @@ int little_solve(qcd_dfl d, const double2 *u, double2 *x, int n, double tol, int
             // w = r - A_EO M1 r
             DFL_TRY(rows(Rows{d->M1, nullptr, 8, 0, 8, rk, o_nb, nh, nullptr, nullptr, 0, q, nullptr, nh, 1.0}));
             DFL_TRY(rows(Rows{d->A, erow, 9, 1, 8, q, e_nb, nh, rk, nullptr, nh, wk, nullptr, nh, -1.0}));
-            const int at = k % look;   // this step's place among those of the look
-            double *mine = one + (size_t)at * n * GMAX;
+            double *mine = one + (size_t)(poll ? at : 0) * n * GMAX;   // its place among the steps of the look
             {
                 ProfScope ps(PROF_BLAS, s);
                 const dim3 grid(G, n);
@@ -518,10 +515,11 @@ int little_solve(qcd_dfl d, const double2 *u, double2 *x, int n, double tol, int
             }
             ++k;
             ++iters;
-            if (poll && (at + 1 == look || k == nkv || iters == maxit)) {
-                DFL_TRY(little_norms(one, G, n * (at + 1), norms, s));
-                DFL_TRY(fetch(norms, n * (at + 1)));
-                for (int c = 0; c <= at && !done; ++c) {
+            ++at;
+            if (poll && (at == want || k == nkv || iters == maxit)) {
+                DFL_TRY(little_norms(one, G, n * at, norms, s));
+                DFL_TRY(fetch(norms, n * at));
+                for (int c = 0; c < at && !done; ++c) {
                     done = true;
                     worst = 0;
                     for (int i = 0; i < n; ++i) {
@@ -530,10 +528,12 @@ int little_solve(qcd_dfl d, const double2 *u, double2 *x, int n, double tol, int
                         if (!(rel <= tol)) done = false;
                     }
                     if (done) {   // the steps after this one do not count
-                        iters -= at - c;
-                        k -= at - c;
+                        iters -= at - 1 - c;
+                        k -= at - 1 - c;
                     }
                 }
+                at = 0;
+                want = std::min(look, next_look(iters, worst, tol));
             }
         }
         DFL_TRY(accum(k));

@@ -69,3 +69,29 @@ def test_solve_without_little_steps(maxit):
             assert float((x[i] - ref[i]).norm() / ref[i].norm()) <= 1e-9, (scale, i)
     d.close()
     fld.close()
+
+
+@pytest.mark.parametrize("geometry,n", [(((8, 8, 8, 8), (2, 2, 2, 2)), 1), (((16, 16, 16, 16), (4, 4, 4, 4)), 5)])
+def test_polled_solve_stops_at_the_step_that_converged(geometry, n):
+    """Loose and tight tolerances: the residual is reached (to the rounding of the
+    product, 1e-12), and one step fewer does not reach it."""
+    import torch
+    import paper_1605_00564_amd as dfl
+    dims, block = geometry
+    fld = dfl.Field(dims, block, 0.120, 1.0, synth.gauge_field(dims, 0.3, 2))
+    d = dfl.Deflation(fld, Ns=12, ninv=2, seed=21)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    v = torch.randn((n, d.Nb, d.Ns), dtype=torch.complex128, device="cuda", generator=g)
+    last = 0
+    for tol in (0.9, 0.3, 0.1, 0.03, 1e-2, 1e-3, 1e-5, 1e-7, 1e-9):
+        w, iters = d.little_solve(v, tol=tol)
+        res = (d.little_apply(w) - v).flatten(1).norm(dim=1) / v.flatten(1).norm(dim=1)
+        assert float(res.max()) <= tol + 1e-12 and iters >= max(1, last), (tol, iters)
+        last = iters
+        if iters > 1:
+            w, fewer = d.little_solve(v, tol=tol, maxit=iters - 1)
+            res = (d.little_apply(w) - v).flatten(1).norm(dim=1) / v.flatten(1).norm(dim=1)
+            assert fewer == iters - 1 and float(res.max()) > tol - 1e-12, (tol, iters)
+    assert last > 4
+    d.close()
+    fld.close()
