@@ -51,78 +51,103 @@ struct Rows {
     double sgn;
 };
 
-// A complex GEMM (N_s x nd N_s) (nd N_s x n) per row on the FP64 matrix cores: a
-// workgroup takes one row, 16 of its N_s and a tile of right-hand sides; its RW
-// waves take every RW-th group of four columns (of all nd couplings in one list)
-// and are added through LDS in order.  With M = a + ib, v = c + id, Re = ac - bd
-// and Im = ad + bc as real 16x16x4 products.  Wide tile: 16 right-hand sides, four
-// products; narrow tile: 8, whose real and imaginary parts are neighbouring
-// columns, two products.  Lane L supplies M[row L % 16][k L / 16] and v[k L / 16]
-// [column L % 16] and receives out[row L / 16 + 4 i][column L % 16].
-// What bounds it is the latency of its loads (slot, then vector), hence the loads
-// of four steps before their products, and four waves per row where the rows
-// alone do not fill the card.  All nine couplings, us, before: one wave per row,
-// one step's loads at a time:
-//   16^3 x 32, 4^4, N_s = 12: n = 1 12.4 -> 11.3, n = 24 14.0 -> 11.4
-//   24^3 x 48, 4^4, N_s = 12: n = 1 24.2 -> 17.7, n = 12 25.9 -> 24.6, n = 40 58.0 -> 51.7
-//   24^3 x 48, 6^4, N_s = 20: n = 1 23.9 -> 11.6, n = 24 31.4 -> 25.3
-constexpr int RU = 4;
+// A complex GEMM (N_s x nd N_s) (nd N_s x n) per row on the FP64 matrix cores, in
+// tiles of 16 of a row's N_s by some right-hand sides.  With M = a + ib, v = c + id,
+// Re = ac - bd and Im = ad + bc as real 16x16x4 products.  Wide tile: 16 right-hand
+// sides, four products; narrow tile: 8, whose real and imaginary parts are
+// neighbouring columns, two products.  Lane L supplies M[row L % 16][k L / 16] and
+// v[k L / 16][column L % 16] and receives out[row L / 16 + 4 i][column L % 16].
+// RW = 4: few tiles, bound by the latency of their loads (slot, then vector).  The
+// waves of a workgroup share a tile, each taking every fourth group of four columns
+// (of all nd couplings in one list) with the loads of four steps before their
+// products, and are added through LDS in order.
+// RW = 1: tiles enough to fill the device, bound by the matrix cores and the L2.  A
+// workgroup takes four tiles (one wave per workgroup left the launch of workgroups
+// as the bound), a wave walks coupling by coupling, the loads of three steps before
+// their products.
+// All nine couplings, us, one wave per row and one step's loads at a time / now:
+//   16^3 x 32, 4^4, N_s = 12: n = 1 10.6 / 9.0, n = 24 11.6 / 9.7
+//   24^3 x 48, 4^4, N_s = 12: n = 1 22.7 / 13.9, n = 12 24.7 / 19.9, n = 25 34.1 / 33.9, n = 40 57.0 / 45.4
+//   24^3 x 48, 4^4, N_s = 20: n = 1 49.7 / 32.9, n = 12 51.2 / 49.3, n = 25 87.6 / 84.4, n = 40 133 / 121
+//   24^3 x 48, 6^4, N_s = 20: n = 1 22.8 / 10.3, n = 24 29.9 / 23.3
+constexpr int RU = 4, RU1 = 3;   // steps in flight
 template <int RW, bool WIDE>
-__global__ void __launch_bounds__(64 * RW) k_little_rows(Rows a, int nrows, int Ns, int n, int nmt, int ng) {
+__global__ void __launch_bounds__(64 * ROW_WAVES) k_little_rows(Rows a, int nrows, int Ns, int n, int nmt, int ng) {
     constexpr int TR = WIDE ? 16 : 8;   // right-hand sides of a tile
-    __shared__ double red[RW][WIDE ? 2 : 1][16][17];
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // the tiles of a row are eight workgroups apart: one XCD, whose L2 then holds M
-    const int per = nmt * ng, i = (blockIdx.x / (8 * per)) * 8 + blockIdx.x % 8, rem = (blockIdx.x / 8) % per;
-    if (i >= nrows) return;
-    const int m0 = (rem / ng) * 16, r0 = (rem % ng) * TR;
+    __shared__ double red[ROW_WAVES][WIDE ? 2 : 1][16][17];
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = wv % RW;
+    const RowTile t = row_tile(blockIdx.x, wv / RW, ROW_WAVES / RW, nmt, ng);
+    const bool live = t.row < nrows;
+    const int i = live ? t.row : nrows - 1, m0 = t.m * 16, r0 = t.r * TR;
     const int row = lane & 15, kk = lane >> 4;
     const bool mv = m0 + row < Ns, im = row & 1;
     const size_t NN = (size_t)Ns * Ns;
     const double2 *M = a.M + ((size_t)(a.mrow ? a.mrow[i] : i) * a.ND + a.d0) * NN + (size_t)(mv ? m0 + row : 0) * Ns;
     const double2 *v = a.v + (size_t)min(r0 + (WIDE ? row : row / 2), n - 1) * a.nv * Ns;   // from n on: not used
     const int *slot = a.slot ? a.slot + (size_t)i * a.nd : nullptr;
-    const int nl = (Ns + 3) / 4, steps = a.nd * nl;
     d4v x = {0, 0, 0, 0}, y = {0, 0, 0, 0}, z = {0, 0, 0, 0}, w = {0, 0, 0, 0};
-    for (int s0 = wave; s0 < steps; s0 += RW * RU) {
-        double2 ma[RU], vb[RU];
+    auto products = [&](const double2 &m, const double2 &b) {
+        x = __builtin_amdgcn_mfma_f64_16x16x4f64(m.x, !WIDE && im ? b.y : b.x, x, 0, 0, 0);
+        y = __builtin_amdgcn_mfma_f64_16x16x4f64(m.y, !WIDE && im ? b.x : -b.y, y, 0, 0, 0);
+        if constexpr (WIDE) {
+            z = __builtin_amdgcn_mfma_f64_16x16x4f64(m.x, b.y, z, 0, 0, 0);
+            w = __builtin_amdgcn_mfma_f64_16x16x4f64(m.y, b.x, w, 0, 0, 0);
+        }
+    };
+    if constexpr (RW == 1) {
+        for (int d = 0; d < a.nd; ++d) {
+            const double2 *Md = M + d * NN, *vd = v + (size_t)(slot ? slot[d] : i) * Ns;
+            for (int l0 = 0; l0 < Ns; l0 += 4 * RU1) {
+                double2 ma[RU1], vb[RU1];
 #pragma unroll
-        for (int u = 0; u < RU; ++u) {
-            const int st = s0 + u * RW;
-            ma[u] = vb[u] = make_double2(0.0, 0.0);
-            if (st < steps) {
-                const int d = st / nl, l = (st - d * nl) * 4 + kk;
-                if (l < Ns) {
-                    if (mv) ma[u] = M[d * NN + l];
-                    vb[u] = v[(size_t)(slot ? slot[d] : i) * Ns + l];
+                for (int u = 0; u < RU1; ++u) {
+                    const int l = l0 + 4 * u + kk;
+                    ma[u] = vb[u] = make_double2(0.0, 0.0);
+                    if (l < Ns) {
+                        if (mv) ma[u] = Md[l];
+                        vb[u] = vd[l];
+                    }
                 }
+#pragma unroll
+                for (int u = 0; u < RU1; ++u)
+                    if (l0 + 4 * u < Ns) products(ma[u], vb[u]);
             }
         }
+    } else {
+        const int nl = (Ns + 3) / 4, steps = a.nd * nl;
+        for (int s0 = wave; s0 < steps; s0 += RW * RU) {
+            double2 ma[RU], vb[RU];
 #pragma unroll
-        for (int u = 0; u < RU; ++u) {
-            const double2 b = vb[u];
-            x = __builtin_amdgcn_mfma_f64_16x16x4f64(ma[u].x, !WIDE && im ? b.y : b.x, x, 0, 0, 0);
-            y = __builtin_amdgcn_mfma_f64_16x16x4f64(ma[u].y, !WIDE && im ? b.x : -b.y, y, 0, 0, 0);
-            if constexpr (WIDE) {
-                z = __builtin_amdgcn_mfma_f64_16x16x4f64(ma[u].x, b.y, z, 0, 0, 0);
-                w = __builtin_amdgcn_mfma_f64_16x16x4f64(ma[u].y, b.x, w, 0, 0, 0);
+            for (int u = 0; u < RU; ++u) {
+                const int st = s0 + u * RW;
+                ma[u] = vb[u] = make_double2(0.0, 0.0);
+                if (st < steps) {
+                    const int d = st / nl, l = (st - d * nl) * 4 + kk;
+                    if (l < Ns) {
+                        if (mv) ma[u] = M[d * NN + l];
+                        vb[u] = v[(size_t)(slot ? slot[d] : i) * Ns + l];
+                    }
+                }
             }
+#pragma unroll
+            for (int u = 0; u < RU; ++u) products(ma[u], vb[u]);
         }
     }
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        red[wave][0][kk + 4 * q][row] = x[q] + y[q];
-        if constexpr (WIDE) red[wave][1][kk + 4 * q][row] = z[q] + w[q];
+        red[wv][0][kk + 4 * q][row] = x[q] + y[q];
+        if constexpr (WIDE) red[wv][1][kk + 4 * q][row] = z[q] + w[q];
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < 16 * TR; e += 64 * RW) {
+    for (int e = wave * 64 + lane; e < 16 * TR; e += 64 * RW) {
         const int mo = e & 15, ro = e >> 4;   // consecutive threads along N_s
-        if (m0 + mo >= Ns || r0 + ro >= n) continue;
+        if (!live || m0 + mo >= Ns || r0 + ro >= n) continue;
         double2 o = make_double2(0, 0);
 #pragma unroll
         for (int p = 0; p < RW; ++p) {
-            o.x += red[p][0][mo][WIDE ? ro : 2 * ro];
-            o.y += WIDE ? red[p][WIDE][mo][ro] : red[p][0][mo][2 * ro + 1];
+            const auto &part = red[wv - wave + p];
+            o.x += part[0][mo][WIDE ? ro : 2 * ro];
+            o.y += WIDE ? part[WIDE][mo][ro] : part[0][mo][2 * ro + 1];
         }
         o.x *= a.sgn;
         o.y *= a.sgn;
@@ -136,28 +161,25 @@ __global__ void __launch_bounds__(64 * RW) k_little_rows(Rows a, int nrows, int 
 }
 
 int rows_launch(const Rows &a, int nrows, int Ns, int n, hipStream_t s) {
-    // nd N_s complex multiply-adds per row entry and right-hand side; M read
-    // once per tile
-    // narrow tiles where they hold fewer columns: 24 right-hand sides, 24^3 x 48:
-    // 36.1 us against 41.4; 12: wide 24.6 against 27.7
-    const bool wide = n > 8 && (n <= 16 || n > 24);
-    const int nmt = (Ns + 15) / 16, ng = wide ? (n + 15) / 16 : (n + 7) / 8;
+    const RowTiles t = row_tiles(nrows, Ns, n);
+    // nd N_s complex multiply-adds per row entry and right-hand side; M read once
+    // per group of right-hand sides
     ProfScope ps(PROF_LITTLE, s, 8.0 * a.nd * Ns * Ns * nrows * n,
-                 16.0 * Ns * nrows * ((double)a.nd * Ns * ng + 2.0 * n), (double)Ns * nrows * n);
-    const unsigned grid = (unsigned)((nrows + 7) / 8) * 8 * nmt * ng;
-    // one wave per tile from 3 waves per SIMD on: 7776 tiles (24^3 x 48, n = 40)
-    // 51.7 us against 61.0 of four, 2592 (n = 1) 18.0 against 17.5, 512 14.4 against 11.0
-    if ((long)nrows * nmt * ng <= 3072) {
-        if (wide)
-            k_little_rows<4, true><<<grid, 256, 0, s>>>(a, nrows, Ns, n, nmt, ng);
+                 16.0 * Ns * nrows * ((double)a.nd * Ns * t.ng + 2.0 * n), (double)Ns * nrows * n);
+    const unsigned grid = row_workgroups(nrows, ROW_WAVES / t.waves, t.nmt, t.ng);
+#define DFL_ROWS(RW, WIDE) k_little_rows<RW, WIDE><<<grid, 64 * ROW_WAVES, 0, s>>>(a, nrows, Ns, n, t.nmt, t.ng)
+    if (t.waves == 1) {
+        if (t.wide)
+            DFL_ROWS(1, true);
         else
-            k_little_rows<4, false><<<grid, 256, 0, s>>>(a, nrows, Ns, n, nmt, ng);
+            DFL_ROWS(1, false);
     } else {
-        if (wide)
-            k_little_rows<1, true><<<grid, 64, 0, s>>>(a, nrows, Ns, n, nmt, ng);
+        if (t.wide)
+            DFL_ROWS(ROW_WAVES, true);
         else
-            k_little_rows<1, false><<<grid, 64, 0, s>>>(a, nrows, Ns, n, nmt, ng);
+            DFL_ROWS(ROW_WAVES, false);
     }
+#undef DFL_ROWS
     DFL_HIP(hipGetLastError());
     return 0;
 }

@@ -2,7 +2,10 @@
 C++ under the address and undefined-behaviour sanitizers: when the host looks at
 the norms.  On residuals that fall by a constant factor no step is run beyond the
 one that converged, save up to the first look of a solve that gains more than a
-digit a step, and looks are no more than one in four steps and two."""
+digit a step, and looks are no more than one in four steps and two.  How a product
+is split: every tile taken once, a workgroup's four waves on one tile as long as
+the tiles do not fill the device and on a tile each beyond (a wave alone in its
+workgroup made large products slower than they had been)."""
 
 import os
 import shutil
@@ -38,3 +41,13 @@ def test_looks(tmp_path):
         assert looks <= -(-need // 4) + 2, (tol, rate, need, looks)
         if tol >= 0.1:
             assert steps == need, (tol, rate, need, steps)
+
+
+def test_row_tiles(tmp_path):
+    cases = [(r, ns, n) for r in (1, 7, 8, 16, 128, 648, 1296, 2592, 8192) for ns in (1, 12, 16, 17, 20, 40)
+             for n in (1, 8, 9, 16, 17, 24, 25, 40)]
+    out = _run(tmp_path, "row_tiles_check.cpp", [f"{r} {s} {n}\n" for r, s, n in cases])
+    assert len(out) == len(cases)
+    for (r, ns, n), (waves, nmt, ng, ok) in zip(cases, out):
+        assert ok, (r, ns, n)
+        assert waves == (4 if r * nmt * ng <= 2048 else 1), (r, ns, n)
