@@ -457,7 +457,8 @@ int gauss_smear(qcd_field f, const void *in, void *out, int nrhs, qcd_prec io, d
  * QCD_TUNE_DIRAC_CANON    dirac_apply on 16-byte aligned, non-overlapping
  *                         vectors of the operator's own vector type:
  *                         1 = on the canonical vectors themselves, with no
- *                         conversions, 2 = converted to the internal layout
+ *                         conversions (blocks with an extent of twice a prime
+ *                         above 128 excepted), 2 = converted to the internal layout
  *                         and back around the stencil that the other knobs
  *                         choose, 0 = as 1 while every stencil knob has its
  *                         default, else as 2.  An autotuner sets 2 while it

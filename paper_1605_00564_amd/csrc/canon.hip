@@ -12,6 +12,7 @@
 // third of each line per instruction, and each line twice (once per parity).
 #include <type_traits>
 
+#include "block_tables.h"
 #include "internal.h"
 
 namespace dfl {
@@ -362,14 +363,16 @@ bool canon_aligned(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u
 
 // Whether the operator runs on the canonical vectors themselves: they hold the
 // stencil's own vector type, are 16-byte aligned and do not overlap (staged
-// copies would make an overlap harmless), and the handle asks for it or leaves
-// every launch choice of the internal-layout stencils at its default.
+// copies would make an overlap harmless), the block shape gives tiles that fill a
+// workgroup, and the handle asks for it or leaves every launch choice of the
+// internal-layout stencils at its default.
 bool canon_route(qcd_field f, const void *in, const void *out, int nrhs, qcd_prec io, qcd_prec storage, qcd_prec vin,
                  qcd_prec vout) {
     if (vin != io || vout != io || (io == QCD_F64) != (storage == QCD_F64)) return false;
     if (storage != QCD_F64 && storage != QCD_F32 && storage != QCD_F16 && storage != QCD_BF16) return false;
     const bool defaults = f->st_block == 1 && f->st_rg == 0 && f->st_order == 1 && f->st_nr == 0 && f->st_linklds == 1;
     if (f->st_canon == 2 || (f->st_canon == 0 && !defaults)) return false;
+    if (!tiles_fill(f->tile_pos, CANON_TILE)) return false;
     if (!canon_aligned(in) || !canon_aligned(out)) return false;
     const size_t bytes = (size_t)nrhs * f->g.V * (io == QCD_F64 ? 192 : 96);
     const char *a = static_cast<const char *>(in), *b = static_cast<const char *>(out);

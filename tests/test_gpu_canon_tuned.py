@@ -59,3 +59,19 @@ def test_canonical_knob():
             fld.tune(F.TUNE_DIRAC_CANON, value)
         assert e.value.code == -1
     fld.close()
+
+
+def test_blocks_whose_tiles_do_not_fill_a_workgroup_are_converted():
+    """1048 positions per parity, 8 x 131: the tiles would hold 8 of 128."""
+    torch, dfl, _, _ = _handle()
+    fld = dfl.Field((4, 4, 4, 524), (2, 2, 2, 262), 0.124, 1.5, synth.gauge_field((4, 4, 4, 524), 0.4, 1))
+    ref = dfl.Field((4, 4, 4, 524), (2, 2, 2, 2), 0.124, 1.5, synth.gauge_field((4, 4, 4, 524), 0.4, 1))
+    g = torch.Generator(device="cuda").manual_seed(4)
+    x = torch.randn((2, fld.V, 4, 3), dtype=torch.complex128, device="cuda", generator=g)
+    y = dfl.dirac_apply(ref, x)
+    for canon in (0, 1, 2):
+        fld.tune(dfl.Field.TUNE_DIRAC_CANON, canon)
+        conv, z = _converted(dfl, fld, x, 0)
+        assert conv and float((z - y).norm() / y.norm()) < 1e-14, canon
+    fld.close()
+    ref.close()
