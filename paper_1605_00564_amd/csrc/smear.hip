@@ -24,6 +24,7 @@
 #include <cmath>
 
 #include "internal.h"
+#include "smear_rules.h"
 
 namespace dfl {
 
@@ -399,7 +400,7 @@ int gauss_run(qcd_field f, const CT *in, CT *out, int n, double kappa, int n_ite
     k_split<<<dim3((unsigned)(V / 64), n), 256, 0, s>>>(in, a, V);
     for (int it = 0; it < n_iter; ++it) {
         // groups of four vectors, then the others
-        const int n4 = n / 4, rest = n % 4;
+        const int n4 = gauss_groups(V, n), rest = n - 4 * n4;
         if (n4)
             k_gauss_step4<<<dim3((unsigned)(V / 64), n4), 64 * GW, 0, s>>>(a, b, U, box, V, kappa, norm);
         if (rest) {
