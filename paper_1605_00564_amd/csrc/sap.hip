@@ -645,7 +645,7 @@ static int run_sap(qcd_field f, int ncy, int nmr, const void *eta, void *psi, in
 #define DFL_SAP_LAUNCH(LDSV, KSV, MAXT, VBHC)                                                                  \
     {                                                                                                          \
         auto kern = k_sap_sweep<S, R, LF, CF, LDSV, KSV, MAXT, VBHC, 1, SI>;                                   \
-        size_t sh = LDSV ? (VBHC < 0 ? lds / Vbh * -VBHC : lds) : 0;                                                                            \
+        size_t sh = LDSV ? (VBHC < 0 ? lds / Vbh * -VBHC : lds) : 0;                                           \
         if (LDSV && sh > 64 * 1024) (void)hipFuncSetAttribute((const void *)kern,                              \
                                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh); \
         kern<<<grid, NT, sh, s>>>(DFL_SAP_ARGS);                                                               \
@@ -665,13 +665,17 @@ static int run_sap(qcd_field f, int ncy, int nmr, const void *eta, void *psi, in
                 // a bound of 768 threads (e.g. 6^4 blocks, 704) leaves 168
                 // registers per lane where 1024 would cap them at 128
                 else if (NT <= 768) {
-                    // where one workgroup fills the LDS anyway, its component
-                    // planes take a fixed stride, so that they sit at immediate
-                    // offsets (16 bits: 11 planes of 744 complex at most) as with
-                    // the compile-time block sizes.  Addresses in registers made
-                    // the sweep spill: 6^4 blocks, 24^3 x 48, BF16, 6 rhs, 10
-                    // sweeps 11.8 -> 6.3 ms.  Up to 384 sites two workgroups
-                    // share the LDS and the exact stride stays
+                    // From seven waves on, one workgroup is all that a CU holds:
+                    // its registers (137 to 168 per lane) allow twelve waves, and
+                    // from 427 sites on so does the LDS.  Its component planes
+                    // take a fixed stride, so that they sit at immediate offsets
+                    // (16 bits: 11 planes of 744 complex at most) as with the
+                    // compile-time block sizes.  Addresses in registers made the
+                    // sweep spill: 6^4 blocks, 24^3 x 48, BF16, 6 rhs, 10 sweeps
+                    // 11.8 -> 6.3 ms; 2 x 4 x 10 x 10 blocks (400 sites), where
+                    // the exact stride would leave LDS for a second workgroup,
+                    // FP32, 5 rhs 2.70 -> 2.47 ms.  Up to 384 sites two
+                    // workgroups are resident and the exact stride stays
                     if constexpr (sizeof(R) == 4) {
                         if (NT > 384 && Vbh <= 744) {
                             DFL_SAP_LAUNCH(true, 1, 768, -744)
