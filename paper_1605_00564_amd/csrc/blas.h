@@ -22,8 +22,6 @@ template <class E> int blas_gs_sub(E *W, const E *rho, long ne, int n, int k, co
 template <class E> int blas_scal_update(E *wk, E *rho, long ne, int n, const double *coef, double *part,
                                         double *out, hipStream_t s);
 template <class E> int blas_norm2(const E *v, long ne, int n, double *part, double *out, hipStream_t s);
-// y += sgn * a_rhs * x
-template <class E> int blas_caxpy(E *y, const E *x, long ne, int n, const double *a, double sgn, hipStream_t s);
 template <class E> int blas_zero(E *y, long ne, int n, hipStream_t s);
 int blas_resid(const double2 *b, const double2 *t, double2 *r, long ne, int n, double *part, double *out,
                hipStream_t s);

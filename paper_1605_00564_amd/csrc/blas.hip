@@ -215,16 +215,6 @@ __global__ void k_accum_d(double2 *__restrict__ x, const double2 *__restrict__ Z
     x[(size_t)r * ne + t] = a;
 }
 
-// y = a * x + y (complex a per rhs, given as (re, im) pairs), FP64 or FP32 elements
-template <class E>
-__global__ void k_caxpy(E *__restrict__ y, const E *__restrict__ x, long ne, const double *__restrict__ a, double sgn) {
-    const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= ne) return;
-    const int r = blockIdx.y;
-    const double ar = -sgn * a[2 * r], ai = -sgn * a[2 * r + 1];
-    y[(size_t)r * ne + t] = esub(y[(size_t)r * ne + t], ar, ai, x[(size_t)r * ne + t]);
-}
-
 template <class E>
 __global__ void k_zero(E *__restrict__ y, long ne) {
     const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -386,14 +376,6 @@ int blas_accum_d(double2 *x, const double2 *Z, long ne, int n, int k, const doub
 }
 
 template <class E>
-int blas_caxpy(E *y, const E *x, long ne, int n, const double *a, double sgn, hipStream_t s) {
-    ProfScope ps(PROF_BLAS, s);
-    k_caxpy<E><<<dim3(nblocks(ne, 256), n), 256, 0, s>>>(y, x, ne, a, sgn);
-    DFL_HIP(hipGetLastError());
-    return 0;
-}
-
-template <class E>
 int blas_zero(E *y, long ne, int n, hipStream_t s) {
     k_zero<E><<<dim3(nblocks(ne, 256), n), 256, 0, s>>>(y, ne);
     DFL_HIP(hipGetLastError());
@@ -452,7 +434,6 @@ size_t scalar_bytes(int n) {
                                 hipStream_t);                                                            \
     template int blas_scal_update<E>(E *, E *, long, int, const double *, double *, double *, hipStream_t); \
     template int blas_norm2<E>(const E *, long, int, double *, double *, hipStream_t);                 \
-    template int blas_caxpy<E>(E *, const E *, long, int, const double *, double, hipStream_t);        \
     template int blas_zero<E>(E *, long, int, hipStream_t);
 DFL_INST(float4)
 DFL_INST(double2)
