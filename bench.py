@@ -190,7 +190,8 @@ STENCIL_MODES = {
 
 def stencil_sweep(lattices, storages, nrhs_list, reps, log, cpu=True):
     """Dirac-operator GB/s and Gflop/s per storage mode and right-hand-side
-    count (kernel time from HIP events; pack/unpack kernels excluded).  With
+    count, on the kernels of the internal layout that the solvers use (kernel
+    time from HIP events; pack/unpack kernels excluded).  With
     cpu, the oracle's FP64 operator on the host is timed beside it (one
     application, one right-hand side, the same algorithmic bytes and flops)."""
     import torch
@@ -199,6 +200,7 @@ def stencil_sweep(lattices, storages, nrhs_list, reps, log, cpu=True):
     for dims in lattices:
         U = synth.gauge_field(dims, 0.4, 1, progress=lambda f: log(f"[sweep] {dims}: gauge field {100 * f:.0f}%"))
         fld = dfl.Field(dims, (4, 4, 4, 4), 0.124, 1.5, torch.from_numpy(U).cuda())
+        fld.tune(dfl.Field.TUNE_DIRAC_CANON, 2)
         V = synth.volume(dims)
         if cpu:
             import oracle
@@ -370,8 +372,8 @@ def post_solve(fld, prop, t0, log, ape=(0.5, 20), gauss=(3.0, 30)):
     ms = _event_ms(lambda: dfl.gauss_smear(fld, prop, kg, n_g, out=sm), 2)
     rec("gauss_smear", ms / n_g, (12 * 2 * 192 + 3 * 144) * V, kappa=kg, iterations=n_g, per="iteration, 12 vectors")
     ms = _event_ms(lambda: dfl.nucleon_2pt(fld, sm, t0), 5)
-    # FP64 arithmetic, 3600 complex multiply-adds per site (the colour sums factored)
-    rec("nucleon_2pt", ms, 2304 * V, flops=28800.0 * V)
+    # FP64 arithmetic, 3024 complex multiply-adds per site (through diquarks)
+    rec("nucleon_2pt", ms, 2304 * V, flops=24192.0 * V)
     for flav in ("u", "d"):
         for tag, ts, P in (("forward", (t0 + T // 4) % T, P_PLUS), ("backward", (t0 - T // 4) % T, P_MINUS)):
             ms = _event_ms(lambda: dfl.nucleon_seq_sources(fld, sm, ts, P, flav), 5)
