@@ -1,6 +1,6 @@
 """Restriction and prolongation at the edges of their launch rules: tiles of
 right-hand sides (1, 4, 5, 8, 9, 16, 17, 25), one and two tiles of fields
-(N_s = 20 > 16), blocks small enough for two waves (2^4: 96 elements) and
+(N_s = 20 > 16), blocks small enough for four waves (2^4: 96 elements) and
 larger ones, deflation blocks of several Schwarz blocks, runs that are not a
 multiple of the stride (2 x 6 x 2 x 2: 12 sites per parity).
 

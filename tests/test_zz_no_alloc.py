@@ -1,9 +1,10 @@
-"""dirac_apply_noalloc (the operator staged in the library's static device
-scratch array, no allocation) against dirac_apply on the same inputs: two
-calls in a row on one GPU, the second with fewer right-hand sides and on a
-smaller lattice, for FP64 and FP16 operator storage; the same kernels run on
-the same data, so the outputs are identical.  Calls needing more staging
-than the array holds are refused."""
+"""dirac_apply_noalloc (the operator without allocation) against dirac_apply on
+the same inputs: two calls in a row on one GPU, the second with fewer
+right-hand sides and on a smaller lattice, for FP64 and FP16 operator storage;
+the same kernels run on the same data, so the outputs are identical.  These
+vectors need no staging; test_gpu_noalloc_staged.py has those that go through
+the library's static device array.  Calls whose staging would be more than the
+array holds are refused."""
 
 import numpy as np
 import pytest
