@@ -59,24 +59,26 @@ def tune_stencil(fld: L.Field, nrhs: int, storage: int = F16, reps: int = 5):
     variants = [(1, 0, 1, 0), (1, 0, 2, 0), (1, 0, 4, 0), (1, 0, 2, 1), (0, 1, 0, 0), (0, 2, 0, 0), (0, 4, 0, 0)]
     times = {}
     fld.tune(L.Field.TUNE_DIRAC_CANON, 2)
-    for blk, rg, nr, llds in variants:
-        fld.tune(L.Field.TUNE_STENCIL_BLOCK, blk)
-        fld.tune(L.Field.TUNE_STENCIL_RG, rg)
-        fld.tune(L.Field.TUNE_STENCIL_NR, nr)
-        fld.tune(L.Field.TUNE_STENCIL_LINKLDS, llds)
-        L.dirac_apply(fld, x, storage=storage, out=y)
-        _sync()
-        t = time.perf_counter()
-        for _ in range(reps):
+    try:
+        for blk, rg, nr, llds in variants:
+            fld.tune(L.Field.TUNE_STENCIL_BLOCK, blk)
+            fld.tune(L.Field.TUNE_STENCIL_RG, rg)
+            fld.tune(L.Field.TUNE_STENCIL_NR, nr)
+            fld.tune(L.Field.TUNE_STENCIL_LINKLDS, llds)
             L.dirac_apply(fld, x, storage=storage, out=y)
-        _sync()
-        times[(blk, rg, nr, llds)] = (time.perf_counter() - t) / reps
+            _sync()
+            t = time.perf_counter()
+            for _ in range(reps):
+                L.dirac_apply(fld, x, storage=storage, out=y)
+            _sync()
+            times[(blk, rg, nr, llds)] = (time.perf_counter() - t) / reps
+    finally:
+        fld.tune(L.Field.TUNE_DIRAC_CANON, 1)
     best = min(times, key=times.get)
     fld.tune(L.Field.TUNE_STENCIL_BLOCK, best[0])
     fld.tune(L.Field.TUNE_STENCIL_RG, best[1])
     fld.tune(L.Field.TUNE_STENCIL_NR, best[2])
     fld.tune(L.Field.TUNE_STENCIL_LINKLDS, best[3])
-    fld.tune(L.Field.TUNE_DIRAC_CANON, 1)
     return best, times
 
 

@@ -43,6 +43,25 @@ def test_tuned_handle_keeps_the_canonical_operator(storage):
     fld.close()
 
 
+def test_tuning_that_fails_keeps_it_too(monkeypatch):
+    torch, dfl, fld, x = _handle()
+    from paper_1605_00564_amd import tune
+    calls = []
+
+    def third_fails(*args, **kwargs):
+        calls.append(args)
+        if len(calls) == 3:
+            raise RuntimeError("the third call")
+        return dfl.dirac_apply(*args, **kwargs)
+
+    monkeypatch.setattr(tune.L, "dirac_apply", third_fails)
+    with pytest.raises(RuntimeError):
+        tune.tune_stencil(fld, 4, storage=1, reps=1)
+    assert len(calls) == 3
+    assert not _converted(dfl, fld, x, 1)[0]
+    fld.close()
+
+
 def test_canonical_knob():
     torch, dfl, fld, x = _handle()
     F = dfl.Field
